@@ -11,8 +11,8 @@
 // independent, so no inter-work-group synchronisation is ever needed):
 //   * a right-hand-side kernel forms t for the plane of every subdomain
 //     (the restriction from the global vector is fused in);
-//   * a GEMM kernel with one wave per (subdomain, 32-row tile, column group)
-//     streams its rows of S_k^{-1} from HBM and t through L2 into MFMA.
+//   * a GEMM kernel with one work-group per (subdomain, row tile, column
+//     group) streams its rows of S_k^{-1} from HBM and t through L2 into MFMA.
 // The GEMM epilogue stores the plane's rows and, once a plane is final,
 // writes the owned nodes to the output (restricted prolongation with a
 // Boolean partition of unity: each output entry is written once, no
@@ -24,14 +24,14 @@
 // accumulate separately, Re = Ar Br - Ai Bi and Im = Ar Bi + Ai Br, six piece
 // products each, and the kernel streams S_k^{-1} at HBM speed.
 //
-// Complex FP64 uses the 16x16x4 FP64 instruction with t in row-major order;
-// the interleaved output columns (Re, Im) of C = A B come from two real
-// products per k-slice, Ar * [Br | Bi] + Ai * [-Bi | Br].
+// Complex FP64 uses the 16x16x4 FP64 instruction with t in row-major order and
+// splits the k range of a tile over the waves of a work-group.
 //
-// Work-groups are one wave.  The hardware hands consecutive work-group ids to
-// the 8 XCDs in turn, so the linear id is mapped such that all waves of one
-// subdomain land on the same XCD and share its L2 copy of t.
+// The hardware hands consecutive work-group ids to the 8 XCDs in turn, so the
+// linear id is mapped such that all work-groups of one subdomain land on the
+// same XCD and share its L2 copy of t.
 #include <algorithm>
+#include <type_traits>
 
 #include "oras_internal.h"
 
@@ -420,63 +420,164 @@ plane_rhs_f64_kernel(const SubDesc* __restrict__ subs, int k, int bwd,
   tvbuf[sd.tv_off * (long long)pad16(s) + idx] = t;
 }
 
-// Y_k (=|-=) S_k^{-1} t for one 32-row tile and 8 NS columns (one wave); a
-// 16-row x 8-column x 4-k step is two instructions (real and imaginary A).
-// Column group cg of the launch starts at column c0base + 8 NS cg.
-template <int NS>
-__global__ void __launch_bounds__(64)
-plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_nt, int ncg, int k,
+// 16-byte loads through a buffer descriptor over an operand that starts at a
+// wave-uniform address (byte offsets: vo per lane, so per wave; every operand
+// is far below 2 GB).  NT = 2 marks a streamed operand non-temporal.
+typedef __amdgpu_buffer_rsrc_t BufRsrc;
+__device__ inline BufRsrc buf_rsrc(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00027000);
+}
+template <int NT> __device__ inline double2 buf_ld(BufRsrc r, int vo, int so) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, NT));
+}
+
+// Y_k (=|-=) S_k^{-1} t for 16 RS rows and one column group per work-group of
+// KS waves, each taking a KS-th of the k range; the waves' sums meet in LDS in
+// a fixed order.  Each wave keeps PF k-steps of both operands in flight.
+//
+// A column group is NC blocks of 16 columns with the real and imaginary parts
+// of the result in separate accumulators (Re += Ar Br - Ai Bi, Im += Ar Bi +
+// Ai Br: four instructions per 16 rows x 16 columns x 4 k, and the factor's
+// sign flip is the only other arithmetic), or, with NC = 0, 8 columns whose
+// parts alternate over the 16 instruction columns (Ar [Br | Bi] + Ai [-Bi |
+// Br]: half the instructions where only 8 columns are left).
+// Column group cg of the launch starts at column c0base + 16 NC cg; columns
+// from s on (a block of 32 over the last 24) read the following row's values
+// and are not stored.
+//
+// What bounds it at 32 columns: with every operand taken from L1 the same
+// kernel runs at 62 TFLOP/s on 320 subdomains of 576-node planes (the rest of
+// the 77 TFLOP/s a large matrix product reaches is ramp, tail and the sums),
+// with the factors streamed from HBM at 51; at 16 and 8 columns the stream,
+// 4.7 - 5.1 TB/s of 5.1 for a large copy.
+template <int NC, int RS, int KS, int PF>
+__global__ void __launch_bounds__(64 * KS)
+plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, int ncg, int k,
                       int bwd, const double2* __restrict__ fac, const double2* __restrict__ tvbuf,
                       double2* __restrict__ ybuf, double2* __restrict__ z, int nx, int ny, int s,
                       int c0base) {
+  constexpr int HW = KS > 1 ? KS / 2 : 1;
+  constexpr int NB = NC ? NC : 1;          // t blocks loaded per k-step
+  constexpr int NA = NC ? 2 * NC : 1;      // accumulators per 16 rows
+  __shared__ double red[HW][RS * NA * 4][64];
   int sub, item;
-  xcd_map(max_nt * ncg, sub, item);
+  xcd_map(max_rg * ncg, sub, item);
   if (sub >= nsub) return;
   const SubDesc sd = subs[sub];
   if (!plane_active(sd, k, bwd)) return;
   const int nt = sd.nt;
-  const int I = item / ncg, c0 = c0base + 8 * NS * (item % ncg);
-  if (I >= nt) return;
+  const int row0 = 16 * RS * (item / ncg), c0 = c0base + 16 * NC * (item % ncg);
+  if (row0 >= sd.P) return;
   const int P = sd.P;
-  const double2* A = fac + sd.fac_off + (long long)k * P * P + (long long)I * nt * (TILE * TILE);
-  const double2* Bm = tvbuf + sd.tv_off * pad16(s) + c0;
-  double2* Yk = ybuf + (sd.y_off + (long long)k * P) * s;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, kk = lane >> 4;
-  const int bn = m >> 1;
   const bool im = (m & 1) != 0;
-  f64x4 acc[2][NS];
+  // k-step g (4 columns) of the row tile starts at entry 128 g, its upper 16
+  // rows at + 64; buffer loads keep the order written here (ordinary loads at
+  // the end of an iteration are moved to the head of the next one, where
+  // their whole latency is waited for)
+  const BufRsrc A = buf_rsrc(fac + sd.fac_off + (long long)k * P * P +
+                             (long long)(row0 / TILE) * nt * (TILE * TILE) + (row0 % TILE) * 4);
+  const BufRsrc B = buf_rsrc(tvbuf + sd.tv_off * pad16(s) + c0);
+  const int ao = (m * 4 + kk) * 16, bo = (kk * s + (NC ? m : m >> 1)) * 16, bstep = 4 * s * 16;
+  f64x4 acc[RS][NA];
 #pragma unroll
-  for (int rs = 0; rs < 2; ++rs)
+  for (int rs = 0; rs < RS; ++rs)
 #pragma unroll
-    for (int ns = 0; ns < NS; ++ns) acc[rs][ns] = f64x4{0, 0, 0, 0};
-  for (int J = 0; J < nt; ++J) {
-    const double2* tA = A + (long long)J * (TILE * TILE);
-#pragma unroll 2
-    for (int q = 0; q < 8; ++q) {
-      const int kc = J * TILE + q * 4 + kk;
-      const double2 a0 = tA[(q * TILE + m) * 4 + kk];
-      const double2 a1 = tA[(q * TILE + 16 + m) * 4 + kk];
-      const double2* brow = Bm + (long long)kc * s + bn;
+    for (int na = 0; na < NA; ++na) acc[rs][na] = f64x4{0, 0, 0, 0};
+  // the wave's share of the 8 nt / PF runs of PF k-steps
+  const int runs = 8 * nt / PF;
+  const int u0 = runs * wv / KS, u1 = runs * (wv + 1) / KS;
+  if (u0 < u1) {
+    double2 ra[PF][RS], rb[PF][NB];
 #pragma unroll
-      for (int ns = 0; ns < NS; ++ns) {
-        const double2 bv = brow[ns * 8];
-        const double b1 = im ? bv.y : bv.x;
-        const double b2 = im ? bv.x : -bv.y;
-        acc[0][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.x, b1, acc[0][ns], 0, 0, 0);
-        acc[0][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.y, b2, acc[0][ns], 0, 0, 0);
-        acc[1][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.x, b1, acc[1][ns], 0, 0, 0);
-        acc[1][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.y, b2, acc[1][ns], 0, 0, 0);
+    for (int d = 0; d < PF; ++d) {
+      const int g = u0 * PF + d;
+#pragma unroll
+      for (int rs = 0; rs < RS; ++rs) ra[d][rs] = buf_ld<2>(A, ao + 1024 * rs, g * 2048);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) rb[d][nb] = buf_ld<0>(B, bo + 256 * nb, g * bstep);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int u = u0; u < u1; ++u) {
+      const int un = min(u + 1, u1 - 1) * PF;   // the last run is fetched again, unused
+#pragma unroll
+      for (int d = 0; d < PF; ++d) {
+        if (NC) {
+#pragma unroll
+          for (int rs = 0; rs < RS; ++rs) {
+            const double ar = ra[d][rs].x, ai = ra[d][rs].y, ni = -ai;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+              const double br = rb[d][nb].x, bi = rb[d][nb].y;
+              f64x4 &re = acc[rs][2 * nb], &mi = acc[rs][NA > 1 ? 2 * nb + 1 : 0];
+              re = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, re, 0, 0, 0);
+              mi = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, mi, 0, 0, 0);
+              re = __builtin_amdgcn_mfma_f64_16x16x4f64(ni, bi, re, 0, 0, 0);
+              mi = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, mi, 0, 0, 0);
+            }
+          }
+        } else {
+          const double2 bv = rb[d][0];
+          const double b1 = im ? bv.y : bv.x;
+          const double b2 = im ? bv.x : -bv.y;
+#pragma unroll
+          for (int rs = 0; rs < RS; ++rs) {
+            acc[rs][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra[d][rs].x, b1, acc[rs][0], 0, 0, 0);
+            acc[rs][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra[d][rs].y, b2, acc[rs][0], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int rs = 0; rs < RS; ++rs) ra[d][rs] = buf_ld<2>(A, ao + 1024 * rs, (un + d) * 2048);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) rb[d][nb] = buf_ld<0>(B, bo + 256 * nb, (un + d) * bstep);
+        // keeps a k-step's waits to its own loads
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
+  // the upper half of the waves hands its sums to the lower half until one is left
+#pragma unroll
+  for (int h = KS / 2; h > 0; h >>= 1) {
+    if (wv >= h && wv < 2 * h) {
+#pragma unroll
+      for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+        for (int na = 0; na < NA; ++na)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) red[wv - h][(rs * NA + na) * 4 + i][lane] = acc[rs][na][i];
+    }
+    __syncthreads();
+    if (wv < h) {
+#pragma unroll
+      for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+        for (int na = 0; na < NA; ++na)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[rs][na][i] += red[wv][(rs * NA + na) * 4 + i][lane];
+    }
+    if (h > 1) __syncthreads();
+  }
+  if (wv > 0) return;
+  // result item i of a lane: row kk + 4 i, instruction column m
+  using OT = typename std::conditional<(NC > 0), double2, double>::type;
+  OT* Yk = reinterpret_cast<OT*>(ybuf + (sd.y_off + (long long)k * P) * s + c0) + m;
+  const int rstride = NC ? s : 2 * s;
   const bool final_plane = bwd || (k == sd.sz - 1);
 #pragma unroll
-  for (int rs = 0; rs < 2; ++rs)
+  for (int rs = 0; rs < RS; ++rs) {
+    OT old[4][NB];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        if (bwd) old[i][nb] = Yk[(long long)(row0 + rs * 16 + kk + 4 * i) * rstride +
+                                 (NC && c0 + 16 * nb + m >= s ? 0 : 16 * nb)];
+        else old[i][nb] = OT{};
+      }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int row = I * TILE + rs * 16 + kk + 4 * i;
-      double* yr = reinterpret_cast<double*>(Yk + (long long)row * s + c0);
+      const int row = row0 + rs * 16 + kk + 4 * i;
       long long zoff = -1;
       if (final_plane && row < sd.p) {
         const int qx = row % sd.sx, qy = row / sd.sx;
@@ -486,48 +587,63 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_nt, in
           zoff = (((long long)gz * ny + gy) * nx + gx) * s + c0;
       }
 #pragma unroll
-      for (int ns = 0; ns < NS; ++ns) {
-        const int idx = ns * 16 + m;
-        double val = acc[rs][ns][i];
-        if (bwd) val = yr[idx] - val;
-        yr[idx] = val;
-        if (zoff >= 0) reinterpret_cast<double*>(z + zoff)[idx] = val;
+      for (int nb = 0; nb < NB; ++nb) {
+        if (NC && c0 + 16 * nb + m >= s) continue;
+        OT val;
+        if constexpr (NC > 0) {
+          val = make_double2(acc[rs][2 * nb][i], acc[rs][2 * nb + 1][i]);
+          if (bwd) val = make_double2(old[i][nb].x - val.x, old[i][nb].y - val.y);
+        } else {
+          val = acc[rs][0][i];
+          if (bwd) val = old[i][nb] - val;
+        }
+        Yk[(long long)row * rstride + 16 * nb] = val;
+        if (zoff >= 0) reinterpret_cast<OT*>(z + zoff)[16 * nb + m] = val;
       }
     }
+  }
 }
 
-// Columns in groups of 8, at most 4 groups per wave: the accumulators of 4
-// keep a wave at 138 registers (three waves per SIMD; 8 groups took 265 and
-// one wave, and re-reading the factors costs less than that).  Fewer groups
-// per wave when a plane step would otherwise launch fewer than 2048 waves
-// (few or small subdomains): every column group is a work-group of the same
-// launch, and the groups of one row tile share its factor rows in L2.  (On
-// 64 subdomains of 28^2-node planes and 32 RHS, 2 groups per wave took
-// 14.6 ms per apply, 1 group 15.7 ms, 4 groups 19.1 ms.)  A remainder of
-// groups goes to a second launch.
+// Columns in blocks of 32; what is left over takes 16 columns, 8 columns (parts
+// interleaved, no padding) or, for 24, a block of 32 with 8 columns unstored
+// (a second launch would read the factors again), in a launch of its own.
+// The split per work-group, measured per plane step with the one-wave,
+// unsplit kernel before it in brackets (160 x 160 x 100 in 320 subdomains and
+// 96^3 in 64 are large, 61 x 47 x 53 in 18 and 32^3 in 8 small):
+//   32 columns: bound by the matrix unit.  16 rows and 4 waves: 456 (497) us
+//   on 320 subdomains, 166 (228) on 64, 50 (98) on 18, 14 (42) on 8; 32 rows
+//   with 8 waves gave 453, 175, 64 and 21.
+//   8 or 16 columns: bound by the factor stream.  With 4 waves per SIMD or
+//   more to launch at 32 rows and 4 waves, that split: 16 columns 337 (358)
+//   and 122 (162) us, 8 columns 297 (321) and 110 (130); below that the chip
+//   would be partly idle, and 16 rows with 8 waves give 16 columns 37 (86) us
+//   on 18 subdomains against 42, 8 columns 30 (82) against 34, and on 8
+//   subdomains 11 (38) against 14.
 void gemm_f64_dispatch(const OrasPlan& pl, int k, int bwd, const double2* fac,
                        const double2* tvbuf, double2* ybuf, double2* z, int nx, int ny, int s,
                        hipStream_t st) {
   const int nsub8 = (pl.nsub + NXCD - 1) / NXCD * NXCD;
-  const int groups = s / RHS_ALIGN;
-  int ns = 4;
-  while (ns > 1 && (long long)nsub8 * pl.max_nt * (groups / ns) < 2048) ns >>= 1;
-  const int full = groups / ns, rem = groups % ns;
-  auto launch = [&](int nsw, int ncg, int c0base) {
-    const dim3 grid((unsigned)(nsub8 * pl.max_nt * ncg));
-#define ORAS_GEMM(NS_)                                                                           \
-  hipLaunchKernelGGL((plane_gemm_f64_kernel<NS_>), grid, dim3(64), 0, st, pl.subs, pl.nsub,     \
-                     pl.max_nt, ncg, k, bwd, fac, tvbuf, ybuf, z, nx, ny, s, c0base)
-    switch (nsw) {
-      case 1: ORAS_GEMM(1); break;
-      case 2: ORAS_GEMM(2); break;
-      case 3: ORAS_GEMM(3); break;
-      default: ORAS_GEMM(4); break;
-    }
-#undef ORAS_GEMM
+  const int groups = s / RHS_ALIGN, full = groups / 4, rem = groups % 4;
+  const bool large = (long long)nsub8 * pl.max_nt * 4 >= 4 * 1024;
+  auto launch = [&](auto nc, auto rs, auto ks, auto pf, int ncg, int c0base) {
+    const int max_rg = pl.max_nt * 2 / rs();
+    hipLaunchKernelGGL((plane_gemm_f64_kernel<nc(), rs(), ks(), pf()>),
+                       dim3((unsigned)(nsub8 * max_rg * ncg)), dim3(64 * ks()), 0, st, pl.subs,
+                       pl.nsub, max_rg, ncg, k, bwd, fac, tvbuf, ybuf, z, nx, ny, s, c0base);
   };
-  if (full > 0) launch(ns, full, 0);
-  if (rem > 0) launch(rem, 1, full * ns * RHS_ALIGN);
+  using std::integral_constant;
+  const integral_constant<int, 0> n0;
+  const integral_constant<int, 1> n1;
+  const integral_constant<int, 2> n2;
+  const integral_constant<int, 4> n4;
+  const integral_constant<int, 8> n8;
+  const int c0 = full * 32;
+  if (full > 0) launch(n2, n1, n4, n4, full, 0);
+  if (rem == 3) launch(n2, n1, n4, n4, 1, c0);
+  if (rem == 2 && large) launch(n1, n2, n4, n2, 1, c0);
+  if (rem == 2 && !large) launch(n1, n1, n8, n2, 1, c0);
+  if (rem == 1 && large) launch(n0, n2, n4, n2, 1, c0);
+  if (rem == 1 && !large) launch(n0, n1, n8, n2, 1, c0);
 }
 
 template <typename Z>
