@@ -246,7 +246,7 @@ oras_status oras_gradient(oras_ctx ctx, const void* u_dev, const void* mu_dev, i
  * weight table's slope times dG/dm = -G / (2 m).  This is the gradient of the
  * map whose weights follow m, so it needs weights that match the current m
  * (after oras_assemble, or oras_set_m_ex with ORAS_WEIGHTS_FOLLOW_M):
- * otherwise ORAS_E_STATE.  Uses scratch of about 7 n doubles. */
+ * otherwise ORAS_E_STATE. */
 oras_status oras_gradient_ex(oras_ctx ctx, const void* u_dev, const void* mu_dev, int nrhs,
                              int flags, double* g_dev);
 

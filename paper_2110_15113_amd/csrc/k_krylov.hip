@@ -1,7 +1,7 @@
 // FP64 kernels of pseudo-block flexible GMRES (paper sec. 2.1: right
 // preconditioning; sec. 2.2: flexible variant and pseudo-block processing;
-// sec. 3.2: classical Gram-Schmidt), plus layout conversion, point sources,
-// receiver sampling and the adjoint gradient.
+// sec. 3.2: classical Gram-Schmidt), plus layout conversion, point sources
+// and receiver sampling.
 //
 // Internal vectors are [node][s] complex128 (right-hand sides fastest).  The
 // Arnoldi basis is stored unnormalised: v_i = scale_i * V_i with a per-column
@@ -409,46 +409,6 @@ __global__ void spread_kernel(const double2* __restrict__ d, long long n, int nr
   }
 }
 
-// g_i = -Re omega^2 q_i sum_c [ wm0_i S_i conj(mu_i) u_i
-//        + sum_{j~i} 1/2 mhat_ij (conj(mu_i) u_j + conj(mu_j) u_i) ],
-// mhat_ij = 1/2 (wm_t,i + wm_t,j) 1/2 (S_i + S_j)
-__global__ void gradient_kernel(OpView V, const double2* __restrict__ qfac,
-                                const double2* __restrict__ u, const double2* __restrict__ mu,
-                                int nrhs, double* __restrict__ gout) {
-  const long long n = (long long)V.nx * V.ny * V.nz;
-  const long long node = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (node >= n) return;
-  const int i = (int)(node % V.nx);
-  const int j = (int)((node / V.nx) % V.ny);
-  const int k = (int)(node / ((long long)V.nx * V.ny));
-  const double2 Si = cmul(cmul(V.px[2 * i + 1], V.py[2 * j + 1]), V.pz[2 * k + 1]);
-  double2 acc = make_double2(0.0, 0.0);
-  {
-    double2 t = make_double2(0.0, 0.0);
-    for (int c = 0; c < nrhs; ++c) cfmaconj(t, mu[(long long)c * n + node], u[(long long)c * n + node]);
-    acc = cscale(cmul(Si, t), V.w7[node * 7 + 3]);
-  }
-  for (int ez = -1; ez <= 1; ++ez)
-    for (int ey = -1; ey <= 1; ++ey)
-      for (int ex = -1; ex <= 1; ++ex) {
-        if (ex == 0 && ey == 0 && ez == 0) continue;
-        const int qi = i + ex, qj = j + ey, qk = k + ez;
-        if (qi < 0 || qi >= V.nx || qj < 0 || qj >= V.ny || qk < 0 || qk >= V.nz) continue;
-        const long long nb = ((long long)qk * V.ny + qj) * V.nx + qi;
-        const int t = 3 + abs(ex) + abs(ey) + abs(ez);
-        const double2 Sj = cmul(cmul(V.px[2 * qi + 1], V.py[2 * qj + 1]), V.pz[2 * qk + 1]);
-        const double2 mh = cscale(cadd(Si, Sj), 0.25 * (V.w7[node * 7 + t] + V.w7[nb * 7 + t]));
-        double2 s2 = make_double2(0.0, 0.0);
-        for (int c = 0; c < nrhs; ++c) {
-          cfmaconj(s2, mu[(long long)c * n + node], u[(long long)c * n + nb]);
-          cfmaconj(s2, mu[(long long)c * n + nb], u[(long long)c * n + node]);
-        }
-        acc = cadd(acc, cscale(cmul(mh, s2), 0.5));
-      }
-  const double2 r = cmul(qfac[node], acc);
-  gout[node] = -V.omega * V.omega * r.x;
-}
-
 template <typename R>
 __global__ void cast_kernel(const double2* __restrict__ src, C<R>* __restrict__ dst,
                             long long count) {
@@ -574,12 +534,6 @@ void launch_spread(const double2* d, long long n, int nrhs, const int* rec, int 
                    int ny, double2* b, hipStream_t st) {
   hipLaunchKernelGGL(spread_kernel, dim3(blocks_for(nrhs, 64)), dim3(64), 0, st, d, n, nrhs, rec,
                      nrec, nx, ny, b);
-}
-void launch_gradient(const OpView& op, const double2* qfac, const double2* u, const double2* mu,
-                     int nrhs, double* g, hipStream_t st) {
-  const long long n = (long long)op.nx * op.ny * op.nz;
-  hipLaunchKernelGGL(gradient_kernel, dim3(blocks_for(n, 128)), dim3(128), 0, st, op, qfac, u, mu,
-                     nrhs, g);
 }
 template <typename R>
 void launch_cast(const double2* src, C<R>* dst, long long count, hipStream_t st) {

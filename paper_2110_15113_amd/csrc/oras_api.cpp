@@ -72,7 +72,7 @@ struct oras_ctx_s {
   int npml = 0, free_surface = 0;
   double c_ref = 0;
   int stencil_prec = ORAS_C128;
-  DevBuf w7, mt, qf, px, py, pz, wtab, scratch8, gradw;
+  DevBuf w7, mt, qf, px, py, pz, wtab, scratch8;
   // node fields of the matrix-free apply, per stencil precision; nodes
   // [mf_lo, mf_hi) per axis lie where every profile value they use is 1
   DevBuf mf4_64, mfim_64, mf4_32, mfim_32, mffac64, mffac32, mftiles;
@@ -163,7 +163,7 @@ struct oras_ctx_s {
     w7.release(); mt.release(); qf.release(); px.release(); py.release(); pz.release();
     mf4_64.release(); mfim_64.release(); mf4_32.release(); mfim_32.release();
     mffac64.release(); mffac32.release(); mftiles.release();
-    wtab.release(); scratch8.release(); gradw.release();
+    wtab.release(); scratch8.release();
     assembled = false;
   }
 };
@@ -1691,17 +1691,9 @@ oras_status oras_gradient_ex(oras_ctx c, const void* u_dev, const void* mu_dev, 
     return fail(c, ORAS_E_STATE,
                 "weight gradient needs weights that follow m (frozen by the last set_m)");
   TRY(check_device(c));
-  launch_gradient(opview(c), c->qf.as<double2>(), (const double2*)u_dev, (const double2*)mu_dev,
-                  nrhs, g_dev, c->stream);
-  if (weights) {
-    const long long sc = weight_grad_scratch(c->nx, c->ny, c->nz);
-    TRY(check_free(c, (double)sc * sizeof(double) - (double)c->gradw.bytes));
-    TRY(dev_alloc(c, c->gradw, (size_t)sc * sizeof(double)));
-    const Table& t = weight_table();
-    launch_weight_gradient(opview(c), c->qf.as<double2>(), c->wtab.as<double>(), t.count, t.g0,
-                           t.dg, (const double2*)u_dev, (const double2*)mu_dev, nrhs,
-                           c->gradw.as<double>(), g_dev, c->stream);
-  }
+  const Table& t = weight_table();
+  launch_gradient(opview(c), c->qf.as<double2>(), c->wtab.as<double>(), t.count, t.g0, t.dg,
+                  weights, (const double2*)u_dev, (const double2*)mu_dev, nrhs, g_dev, c->stream);
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ORAS_OK;

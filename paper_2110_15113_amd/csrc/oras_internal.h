@@ -260,7 +260,10 @@ void launch_sample(const double2* u, long long n, int nrhs, const int* rec, int 
                    int ny, double2* d, hipStream_t st);
 void launch_spread(const double2* d, long long n, int nrhs, const int* rec, int nrec, int nx,
                    int ny, double2* b, hipStream_t st);
-void launch_gradient(const OpView& op, const double2* qfac, const double2* u, const double2* mu,
+// Gradient with respect to m; weights adds the dependence of the stencil
+// weights (table wtab over G = g0 + dg * row) on m.
+void launch_gradient(const OpView& op, const double2* qfac, const double* wtab, int tab_count,
+                     double g0, double dg, bool weights, const double2* u, const double2* mu,
                      int nrhs, double* g, hipStream_t st);
 template <typename R>
 void launch_cast(const double2* src, C<R>* dst, long long count, hipStream_t st);
@@ -328,14 +331,6 @@ template <typename R, typename Z>
 void launch_oras_apply_blr(const BlrApply& pl, const C<R>* astore, const C<R>* lca, C<R>* ybuf,
                            C<R>* bt, const double2* v, const double* scale, Z* z, int nx, int ny,
                            int s, hipStream_t st, hipEvent_t* gemm_ev = nullptr);
-
-// Stencil-weight part of the gradient (weights following m): g -= sum_k
-// dw_k/dm Re H_k.  scratch holds weight_grad_scratch(nx, ny, nz) doubles.
-long long weight_grad_scratch(int nx, int ny, int nz);
-void launch_weight_gradient(const OpView& op, const double2* qfac, const double* wtab,
-                            int tab_count, double g0, double dg, const double2* u,
-                            const double2* mu, int nrhs, double* scratch, double* g,
-                            hipStream_t st);
 
 // ------------------------------------------------- shared by entry points --
 // (defined in oras_api.cpp, which owns the context layout)
