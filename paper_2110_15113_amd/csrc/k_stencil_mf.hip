@@ -58,7 +58,7 @@ namespace {
 
 // Tiles of TX x TY x TZ nodes (measured on a 160^3 grid with 32 right-hand
 // sides: 8 x 8 columns beat 16 x 8 and 16 x 4 by 2-6 %; marching 32 planes
-// was no faster per node)
+// was no faster per node); fewer planes on small grids (pick_tiles)
 constexpr int TX = 8;
 constexpr int TY = 8;
 constexpr int TZ = 16;
@@ -121,9 +121,17 @@ enum { FIRST = 0, MID = 1, LAST = 2 };
 
 // PML: tiles the PML reaches (profile factors formed), else PML-free tiles.
 // RC: right-hand sides of the work-group's chunk (a multiple of 8).
-template <typename R, bool PML, int RC, typename Y>
+// PLANAR: x and y are the caller's (nrhs, n) complex128 arrays, s = nrhs (no
+// b; columns from s on are zero and not stored); x is rounded to T on its way
+// into LDS.  Chunks of 16 right-hand sides then (a plane's values wait in
+// registers as complex128, 7 per thread).  On 192 x 192 x 96 nodes and 64
+// right-hand sides in single precision a call takes 3.6 ms, of which the
+// arrays' traffic is 1.4 at the rate of a large copy, against 8.4 ms with
+// passes to and from the internal layout and a rounding pass around it.
+template <typename R, bool PML, int RC, typename Y, bool PLANAR>
 __global__ void __launch_bounds__(NTHREADS)
-stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* __restrict__ x,
+stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles,
+                  const std::conditional_t<PLANAR, double2, C<R>>* __restrict__ x,
                   const double2* __restrict__ b, Y* __restrict__ y, int nx, int ny, int nz,
                   int s, int c_first, int nitems, int per_xcd, int nchunk) {
   using T = C<R>;
@@ -133,7 +141,9 @@ stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* _
   constexpr int UP = U + 1;                     // units per node in LDS: odd, conflict-free
   constexpr int HX = TX + 2, HY = TY + 2;
   constexpr int NU = HX * HY * U;
-  constexpr int NXR = (NU + NTHREADS - 1) / NTHREADS;
+  constexpr int NXV = PLANAR ? HX * HY * RC : NU;   // loads per plane: values or units
+  constexpr int NXR = (NXV + NTHREADS - 1) / NTHREADS;
+  using XV = std::conditional_t<PLANAR, double2, float4>;
   constexpr int CPU = 16 / (int)sizeof(T);      // complex values per 16-byte unit
   static_assert(RT % CPU == 0 || CPU % RT == 0, "lane share of a chunk");
   static_assert(HX * HY <= NTHREADS, "one field node per thread");
@@ -173,7 +183,7 @@ stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* _
   }
 
   // next plane of x and of node fields, staged in registers
-  float4 xr[NXR];
+  XV xr[NXR];
   V4 f4r;
   R fir;
   T fsr;
@@ -182,11 +192,18 @@ stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* _
 #pragma unroll
     for (int j = 0; j < NXR; ++j) {
       const int q = tid + j * NTHREADS;
-      const int u = q % U, hn = q / U;
+      // a planar column's nodes are consecutive along x, a node's columns otherwise
+      const int u = PLANAR ? q / (HX * HY) : q % U, hn = PLANAR ? q % (HX * HY) : q / U;
       const int hi = i0 + hn % HX - 1, hj = j0 + hn / HX - 1;
-      xr[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (q < NU && kin && hi >= 0 && hi < nx && hj >= 0 && hj < ny)
-        xr[j] = reinterpret_cast<const float4*>(x + (((long long)kk * ny + hj) * nx + hi) * s + c0)[u];
+      xr[j] = XV{};
+      if (q < NXV && kin && hi >= 0 && hi < nx && hj >= 0 && hj < ny) {
+        const long long g = ((long long)kk * ny + hj) * nx + hi;
+        if constexpr (PLANAR) {
+          if (c0 + u < s) xr[j] = x[(long long)(c0 + u) * ((long long)nx * ny * nz) + g];
+        } else {
+          xr[j] = reinterpret_cast<const float4*>(x + g * s + c0)[u];
+        }
+      }
     }
   };
   auto fetch_f = [&](int kk) {
@@ -206,9 +223,10 @@ stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* _
 #pragma unroll
     for (int j = 0; j < NXR; ++j) {
       const int q = tid + j * NTHREADS;
-      if (q < NU) {
-        const int u = q % U, hn = q / U;
-        xs[hn / HX][hn % HX][u] = xr[j];
+      if (q < NXV) {
+        const int u = PLANAR ? q / (HX * HY) : q % U, hn = PLANAR ? q % (HX * HY) : q / U;
+        if constexpr (PLANAR) reinterpret_cast<T*>(xs[hn / HX][hn % HX])[u] = ccast<T>(xr[j]);
+        else xs[hn / HX][hn % HX][u] = xr[j];
       }
     }
   };
@@ -330,9 +348,14 @@ stencil_mf_kernel(StencilMF<R> op, const int4* __restrict__ tiles, const C<R>* _
   // output plane k is complete once plane k + 1 has been applied
   auto flush = [&](int k) {
     if (inside && k >= k0 && k < kend) {
-      const long long o = (((long long)k * ny + gj) * nx + gi) * s + c0 + part * RT;
+      const long long g = ((long long)k * ny + gj) * nx + gi, o = g * s + c0 + part * RT;
 #pragma unroll
       for (int q = 0; q < RT; ++q) {
+        if constexpr (PLANAR) {
+          const int c = c0 + part * RT + q;
+          if (c < s) y[(long long)c * ((long long)nx * ny * nz) + g] = ccast<double2>(acc[0][q]);
+          continue;
+        }
         double2 out = make_double2((double)acc[0][q].x, (double)acc[0][q].y);
         if (b) out = csub(b[o + q], out);
         if constexpr (std::is_same<Y, double2>::value) {
@@ -395,36 +418,51 @@ __global__ void mass_fields_kernel(const double* w7, const double2* mt, long lon
   fim[i] = (R)mt[i].y;
 }
 
-template <typename R, bool PML, int RC, typename Y>
-void launch_chunks(const StencilMF<R>& op, const C<R>* x, const double2* b, Y* y, int nx,
-                   int ny, int nz, int s, int c_first, int nchunk, hipStream_t st) {
-  const int lo = PML ? op.nplain : 0, hi = PML ? op.ntiles : op.nplain;
+template <typename R, bool PML, int RC, bool PLANAR, typename X, typename Y>
+void launch_chunks(const StencilMF<R>& op, const StencilTiles& tl, const X* x, const double2* b,
+                   Y* y, int nx, int ny, int nz, int s, int c_first, int nchunk, hipStream_t st) {
+  const int lo = PML ? tl.nplain : 0, hi = PML ? tl.ntiles : tl.nplain;
   if (hi == lo || nchunk == 0) return;
   const int nitems = (hi - lo) * nchunk;
   const int per_xcd = (nitems + NXCD - 1) / NXCD;
-  hipLaunchKernelGGL((stencil_mf_kernel<R, PML, RC, Y>), dim3((unsigned)(per_xcd * NXCD)),
-                     dim3(NTHREADS), 0, st, op, op.tiles + lo, x, b, y, nx, ny, nz, s, c_first,
+  hipLaunchKernelGGL((stencil_mf_kernel<R, PML, RC, Y, PLANAR>), dim3((unsigned)(per_xcd * NXCD)),
+                     dim3(NTHREADS), 0, st, op, tl.tiles + lo, x, b, y, nx, ny, nz, s, c_first,
                      nitems, per_xcd, nchunk);
 }
 
-template <typename R, bool PML, typename Y>
-void launch_kind(const StencilMF<R>& op, const C<R>* x, const double2* b, Y* y, int nx,
-                 int ny, int nz, int s, hipStream_t st) {
-  // chunks of the widest width, then narrower chunks for the rest (s is a
-  // multiple of 8)
-  constexpr int RC = MfChunk<R, PML>::RC;
-  const int full = s / RC;
+template <typename R, bool PML, bool PLANAR, typename X, typename Y>
+void launch_kind(const StencilMF<R>& op, const StencilTiles& tl, const X* x, const double2* b,
+                 Y* y, int nx, int ny, int nz, int s, hipStream_t st) {
+  // chunks of the widest width, then narrower chunks for the rest (columns
+  // rounded up to a multiple of 8)
+  constexpr int RC = PLANAR ? 16 : MfChunk<R, PML>::RC;
+  const int sp = (s + RHS_ALIGN - 1) / RHS_ALIGN * RHS_ALIGN;
+  const int full = sp / RC;
   int c = full * RC;
-  launch_chunks<R, PML, RC, Y>(op, x, b, y, nx, ny, nz, s, 0, full, st);
+  launch_chunks<R, PML, RC, PLANAR>(op, tl, x, b, y, nx, ny, nz, s, 0, full, st);
   if constexpr (RC > 16) {
-    if (s - c >= 16) {
-      launch_chunks<R, PML, 16, Y>(op, x, b, y, nx, ny, nz, s, c, 1, st);
+    if (sp - c >= 16) {
+      launch_chunks<R, PML, 16, PLANAR>(op, tl, x, b, y, nx, ny, nz, s, c, 1, st);
       c += 16;
     }
   }
   if constexpr (RC > 8) {
-    if (s - c >= 8) launch_chunks<R, PML, 8, Y>(op, x, b, y, nx, ny, nz, s, c, 1, st);
+    if (sp - c >= 8) launch_chunks<R, PML, 8, PLANAR>(op, tl, x, b, y, nx, ny, nz, s, c, 1, st);
   }
+}
+
+// The tallest tiles that give the chip two work-groups per CU, else the lowest
+// ones: a tile of TZ planes marches through TZ + 2, so low tiles cost more
+// arithmetic, but a small grid is one round of work-groups that lasts as long
+// as its march.  16 / 8 / 4 / 2 planes per tile: 96^3, 32 right-hand sides in
+// single precision (1728 tile chunks of 16 planes) 548 / 566 / 606 / 733 us a
+// call; 64^3, 16 (256) 171 / 127 / 125 / 138; 61 x 47 x 53, 5 (192) 122 / 88 /
+// 74 / 77; 32^3, 1 in double (32) 70 / 68 / 50 / 40.
+template <typename R>
+const StencilTiles& pick_tiles(const StencilMF<R>& op, int s) {
+  for (int q = 0; q < STENCIL_LISTS - 1; ++q)
+    if ((long long)op.tl[q].ntiles * ((s + 15) / 16) >= 512) return op.tl[q];
+  return op.tl[STENCIL_LISTS - 1];
 }
 
 }  // namespace
@@ -437,12 +475,13 @@ void launch_mass_fields(const double* w7, const double2* mt, long long n,
                      w7, mt, n, f4, fim);
 }
 
-void stencil_mf_tiles(const int lo[3], const int hi[3], int nx, int ny, int nz,
+void stencil_mf_tiles(const int lo[3], const int hi[3], int nx, int ny, int nz, int list,
                       std::vector<int>& tiles, int& nplain) {
-  const int n[3] = {nx, ny, nz}, t[3] = {TX, TY, TZ};
+  const int tz = TZ >> list;
+  const int n[3] = {nx, ny, nz}, t[3] = {TX, TY, tz};
   std::vector<int> pml;
   tiles.clear();
-  for (int k0 = 0; k0 < nz; k0 += TZ)
+  for (int k0 = 0; k0 < nz; k0 += tz)
     for (int j0 = 0; j0 < ny; j0 += TY)
       for (int i0 = 0; i0 < nx; i0 += TX) {
         const int b0[3] = {i0, j0, k0};
@@ -450,7 +489,7 @@ void stencil_mf_tiles(const int lo[3], const int hi[3], int nx, int ny, int nz,
         for (int a = 0; a < 3; ++a)
           plain = plain && b0[a] >= lo[a] && std::min(b0[a] + t[a], n[a]) <= hi[a];
         std::vector<int>& v = plain ? tiles : pml;
-        v.insert(v.end(), {i0, j0, k0, std::min(k0 + TZ, nz)});
+        v.insert(v.end(), {i0, j0, k0, std::min(k0 + tz, nz)});
       }
   nplain = (int)(tiles.size() / 4);
   tiles.insert(tiles.end(), pml.begin(), pml.end());
@@ -460,14 +499,27 @@ template <typename R, typename Y>
 void launch_stencil_mf(const StencilMF<R>& op, const C<R>* x, const double2* b, Y* y, int nx,
                        int ny, int nz, int s, hipStream_t st) {
   static_assert(RHS_ALIGN == 8, "chunk widths cover multiples of 8");
-  launch_kind<R, false, Y>(op, x, b, y, nx, ny, nz, s, st);
-  launch_kind<R, true, Y>(op, x, b, y, nx, ny, nz, s, st);
+  const StencilTiles& tl = pick_tiles(op, s);
+  launch_kind<R, false, false>(op, tl, x, b, y, nx, ny, nz, s, st);
+  launch_kind<R, true, false>(op, tl, x, b, y, nx, ny, nz, s, st);
+}
+
+template <typename R>
+void launch_stencil_mf_planar(const StencilMF<R>& op, const double2* x, double2* y, int nx, int ny,
+                              int nz, int nrhs, hipStream_t st) {
+  const StencilTiles& tl = pick_tiles(op, nrhs);
+  launch_kind<R, false, true>(op, tl, x, nullptr, y, nx, ny, nz, nrhs, st);
+  launch_kind<R, true, true>(op, tl, x, nullptr, y, nx, ny, nz, nrhs, st);
 }
 
 template void launch_mass_fields<float>(const double*, const double2*, long long, float4*, float*,
                                         hipStream_t);
 template void launch_mass_fields<double>(const double*, const double2*, long long, double4*,
                                          double*, hipStream_t);
+template void launch_stencil_mf_planar<float>(const StencilMF<float>&, const double2*, double2*,
+                                              int, int, int, int, hipStream_t);
+template void launch_stencil_mf_planar<double>(const StencilMF<double>&, const double2*, double2*,
+                                               int, int, int, int, hipStream_t);
 template void launch_stencil_mf<float, double2>(const StencilMF<float>&, const float2*,
                                                 const double2*, double2*, int, int, int, int,
                                                 hipStream_t);

@@ -60,6 +60,8 @@ extern "C" oras_status oras_apply_A_noalloc(oras_ctx c, const void* x_dev, void*
                             std::to_string(NOALLOC_BYTES) + " (n * pad8(nrhs) too large)";
     return oras::set_error(c, ORAS_E_ARG, msg.c_str());
   }
+  oras_status direct = ORAS_OK;
+  if (!oras::apply_A_in_place(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
   const int dev = oras::ctx_device(c);
   void* base = nullptr;
   {

@@ -77,7 +77,7 @@ struct oras_ctx_s {
   // [mf_lo, mf_hi) per axis lie where every profile value they use is 1
   DevBuf mf4_64, mfim_64, mf4_32, mfim_32, mffac64, mffac32, mftiles;
   int mf_lo[3] = {0, 0, 0}, mf_hi[3] = {0, 0, 0};
-  int mf_ntiles = 0, mf_nplain = 0;
+  int mf_first[STENCIL_LISTS] = {}, mf_ntiles[STENCIL_LISTS] = {}, mf_nplain[STENCIL_LISTS] = {};
   bool weights_match_m = false;   // the stencil weights are those of the current m
   double t_assemble = 0;
 
@@ -318,9 +318,13 @@ oras_status build_fields(oras_ctx c) {
     HIP_TRY(c, hipMemcpyAsync(c->mffac32.p, fac32.data(), fac32.size() * sizeof(float2),
                               hipMemcpyHostToDevice, c->stream));
   }
-  std::vector<int> tiles;
-  stencil_mf_tiles(c->mf_lo, c->mf_hi, c->nx, c->ny, c->nz, tiles, c->mf_nplain);
-  c->mf_ntiles = (int)(tiles.size() / 4);
+  std::vector<int> tiles, list;
+  for (int q = 0; q < STENCIL_LISTS; ++q) {
+    stencil_mf_tiles(c->mf_lo, c->mf_hi, c->nx, c->ny, c->nz, q, list, c->mf_nplain[q]);
+    c->mf_first[q] = (int)(tiles.size() / 4);
+    c->mf_ntiles[q] = (int)(list.size() / 4);
+    tiles.insert(tiles.end(), list.begin(), list.end());
+  }
   TRY(dev_alloc(c, c->mftiles, tiles.size() * sizeof(int)));
   HIP_TRY(c, hipMemcpyAsync(c->mftiles.p, tiles.data(), tiles.size() * sizeof(int),
                             hipMemcpyHostToDevice, c->stream));
@@ -329,15 +333,15 @@ oras_status build_fields(oras_ctx c) {
   return ORAS_OK;
 }
 
-template <typename R> StencilMF<R> mf_view(oras_ctx c);
-template <> StencilMF<double> mf_view<double>(oras_ctx c) {
+template <typename R> StencilMF<R> mf_arrays(oras_ctx c);
+template <> StencilMF<double> mf_arrays<double>(oras_ctx c) {
   StencilMF<double> v;
   v.f4 = c->mf4_64.as<double4>();
   v.fim = c->mfim_64.as<double>();
   v.fx = c->mffac64.as<double2>();
   return v;
 }
-template <> StencilMF<float> mf_view<float>(oras_ctx c) {
+template <> StencilMF<float> mf_arrays<float>(oras_ctx c) {
   StencilMF<float> v;
   v.f4 = c->mf4_32.as<float4>();
   v.fim = c->mfim_32.as<float>();
@@ -345,16 +349,12 @@ template <> StencilMF<float> mf_view<float>(oras_ctx c) {
   return v;
 }
 
-// y (internal [n][s], c128 or, in single precision without b, c64) = A x, or
-// b - A x when b is given, with x in the stencil precision R
-template <typename R, typename Y = double2>
-void apply_stencil(oras_ctx c, const C<R>* x, const double2* b, Y* y, int s, hipStream_t st) {
-  StencilMF<R> v = mf_view<R>(c);
+template <typename R> StencilMF<R> mf_view(oras_ctx c) {
+  StencilMF<R> v = mf_arrays<R>(c);
   v.fy = v.fx + 9 * c->nx;
   v.fz = v.fy + 9 * c->ny;
-  v.tiles = c->mftiles.as<int4>();
-  v.ntiles = c->mf_ntiles;
-  v.nplain = c->mf_nplain;
+  for (int q = 0; q < STENCIL_LISTS; ++q)
+    v.tl[q] = {c->mftiles.as<int4>() + c->mf_first[q], c->mf_ntiles[q], c->mf_nplain[q]};
   const Table& t = weight_table();
   const double ih2 = 1.0 / (c->h * c->h);
   // family weights (the same in every row of the table) with the averaging
@@ -363,7 +363,14 @@ void apply_stencil(oras_ctx c, const C<R>* x, const double2* b, Y* y, int s, hip
   v.W2 = t.w[1] * ih2 * 0.125;
   v.W3 = t.w[2] * ih2 * 0.0625;
   v.om2 = c->omega * c->omega;
-  launch_stencil_mf<R, Y>(v, x, b, y, c->nx, c->ny, c->nz, s, st);
+  return v;
+}
+
+// y (internal [n][s], c128 or, in single precision without b, c64) = A x, or
+// b - A x when b is given, with x in the stencil precision R
+template <typename R, typename Y = double2>
+void apply_stencil(oras_ctx c, const C<R>* x, const double2* b, Y* y, int s, hipStream_t st) {
+  launch_stencil_mf<R, Y>(mf_view<R>(c), x, b, y, c->nx, c->ny, c->nz, s, st);
 }
 
 int nblk_for(long long n) {
@@ -579,6 +586,27 @@ oras_status apply_A_staged(oras_ctx c, const void* x_dev, void* y_dev, int nrhs,
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ORAS_OK;
+}
+
+// The caller's layout is read and written by the apply itself, unless the two
+// arrays overlap: then x has to be read in full first.
+bool apply_A_in_place(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
+                      oras_status* st) {
+  const size_t bytes = (size_t)c->n * nrhs * sizeof(double2);
+  const uintptr_t x = (uintptr_t)x_dev, y = (uintptr_t)y_dev;
+  if (x < y + bytes && y < x + bytes) return true;
+  *st = [&]() -> oras_status {
+    if (prec == ORAS_C64)
+      launch_stencil_mf_planar<float>(mf_view<float>(c), (const double2*)x_dev, (double2*)y_dev,
+                                      c->nx, c->ny, c->nz, nrhs, c->stream);
+    else
+      launch_stencil_mf_planar<double>(mf_view<double>(c), (const double2*)x_dev, (double2*)y_dev,
+                                       c->nx, c->ny, c->nz, nrhs, c->stream);
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return ORAS_OK;
+  }();
+  return false;
 }
 
 oras_status set_error(oras_ctx c, oras_status st, const char* msg) { return fail(c, st, msg); }
@@ -1347,6 +1375,8 @@ oras_status oras_subdomain(oras_ctx c, int j, int* nsub, int* box12) {
 
 oras_status oras_apply_A(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec) {
   TRY(oras::check_apply_A(c, x_dev, y_dev, nrhs, prec));
+  oras_status direct = ORAS_OK;
+  if (!oras::apply_A_in_place(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
   const long long s = pad_s(nrhs);
   TRY(dev_alloc(c, c->Bint, (size_t)(c->n * s) * sizeof(double2)));
   TRY(dev_alloc(c, c->Tmp, (size_t)(c->n * s) * sizeof(double2)));

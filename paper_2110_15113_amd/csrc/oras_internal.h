@@ -172,31 +172,41 @@ void launch_field_check(const double* x, long long n, double* out, hipStream_t s
 template <typename R> struct R4;
 template <> struct R4<float> { using type = float4; };
 template <> struct R4<double> { using type = double4; };
+// One tiling of the grid for the apply: tiles (i0, j0, k0, k1), the nplain
+// PML-free ones first (stencil_mf_tiles).
+struct StencilTiles {
+  const int4* tiles = nullptr;
+  int ntiles = 0, nplain = 0;
+};
+constexpr int STENCIL_LISTS = 4;   // tiles of 16, 8, 4 and 2 planes
 template <typename R> struct StencilMF {
   const typename R4<R>::type* f4;
   const R* fim;
   const C<R>* fx;        // factor tables, 9 per node coordinate along each axis
   const C<R>* fy;
   const C<R>* fz;
-  const int4* tiles;     // tiles (i0, j0, k0, k1), PML-free ones first (stencil_mf_tiles)
-  int ntiles, nplain;
+  StencilTiles tl[STENCIL_LISTS];
   double W1, W2, W3;     // stiffness family weights: w1 / h^2, w2 / (8 h^2), w3 / (16 h^2)
   double om2;            // omega^2
 };
 template <typename R>
 void launch_mass_fields(const double* w7, const double2* mt, long long n,
                         typename R4<R>::type* f4, R* fim, hipStream_t st);
-// The apply's tiles as (i0, j0, k0, k1) quadruples, the nplain PML-free ones
+// The apply's tiles (16 >> list planes) as (i0, j0, k0, k1) quadruples, the nplain PML-free ones
 // first (every node within [lo, hi) per axis: all profile values its row
 // uses are 1), then the PML tiles covering the rest of the grid.
-void stencil_mf_tiles(const int lo[3], const int hi[3], int nx, int ny, int nz,
+void stencil_mf_tiles(const int lo[3], const int hi[3], int nx, int ny, int nz, int list,
                       std::vector<int>& tiles, int& nplain);
 // y = A x (or b - A x) in [n][s] layout; y is complex128, or complex64 for
 // the single-precision apply without b (its values are FP32 ones either way).
 template <typename R, typename Y = double2>
 void launch_stencil_mf(const StencilMF<R>& op, const C<R>* x, const double2* b, Y* y, int nx,
                        int ny, int nz, int s, hipStream_t st);
-
+// y = A x on the caller's (nrhs, nz, ny, nx) complex128 arrays, which must not
+// overlap; x is rounded to R first.
+template <typename R>
+void launch_stencil_mf_planar(const StencilMF<R>& op, const double2* x, double2* y, int nx, int ny,
+                              int nz, int nrhs, hipStream_t st);
 
 // Factorisation, one plane for all subdomains.  stats (2 per subdomain plane,
 // zeroed before the first plane) receives the bits of max |S_k|^2 and of
@@ -340,6 +350,10 @@ oras_status check_apply_A(oras_ctx c, const void* x_dev, const void* y_dev, int 
 size_t apply_A_scratch_bytes(oras_ctx c, int nrhs, int prec);
 oras_status apply_A_staged(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
                            double2* xin, double2* yout, float2* x32);
+// false: x and y do not overlap and y = A x was formed straight from the
+// caller's arrays, with the result in *st
+bool apply_A_in_place(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
+                      oras_status* st);
 oras_status set_error(oras_ctx c, oras_status st, const char* msg);
 int ctx_device(oras_ctx c);
 // Records the address of `device`'s copy of the no-alloc scratch array

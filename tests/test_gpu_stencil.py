@@ -78,3 +78,27 @@ def test_matrix_free_apply_after_set_m():
     y64 = S.apply_A(to_dev(x, S), prec=1).cpu().numpy()
     assert _row_err(y128, ref, scale) < FP64_ROW
     assert _row_err(y64, ref, scale) < FP32_ROW
+
+
+# grids whose applies run tiles of 2, 4, 8 and 16 planes (8 x 8 columns, the
+# tallest with 512 work items): 25 x 2, 25 x 11 x 2, 36 x 5 x 3 and 64 x 3 x 3
+# tiles times chunks of 16
+@pytest.mark.parametrize("n,nrhs", [((33, 34, 3), 1), ((33, 34, 41), 17), ((41, 42, 37), 33),
+                                    ((57, 58, 33), 35)])
+def test_apply_of_caller_arrays(n, nrhs):
+    """Every tile height against the oracle's rows; an output that overlaps
+    the input takes the staged path and agrees with the direct one."""
+    need_gpu()
+    w = wl.small_random(n, npml=1, q=70.0, seed=61)
+    S = setup(w, prec=1)
+    x = rand_field((w.nz, w.ny, w.nx), nrhs, 62)
+    C = op.row_coeffs(oracle_fields(w))
+    ref = op.apply_coeffs(C, x)
+    scale = op.apply_coeffs(np.abs(C), np.abs(x)).real
+    for prec, bar in ((2, FP64_ROW), (1, FP32_ROW)):
+        xd = to_dev(x, S)
+        y = S.apply_A(xd, prec=prec)
+        assert _row_err(y.cpu().numpy(), ref, scale) < bar
+        if nrhs * w.nx * w.ny * w.nz * 40 < 5e7:
+            S.apply_A_noalloc(xd, xd, prec=prec)      # in place
+            assert _row_err(xd.cpu().numpy(), ref, scale) < bar
