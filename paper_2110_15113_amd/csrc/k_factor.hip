@@ -23,8 +23,16 @@
 // is recorded):
 //     A_kk <- A_kk^{-1};  A_kJ <- A_kk^{-1} A_kJ;  A_IJ <- A_IJ - A_Ik A_kJ;
 //     A_Ik <- -A_Ik A_kk^{-1}.
-// The trailing update A_IJ -= A_Ik A_kJ, which carries almost all the work,
-// runs on MFMA; the panel and pivot-block steps are small and use VALU.
+// B_j is complex symmetric and so is every S_k.  The elimination keeps that
+// up to signs: A_JI = A_IJ^T where I and J are both eliminated or both not,
+// A_JI = -A_IJ^T otherwise.  So only the tiles with I <= J are kept up to date,
+// which halves the trailing update that carries almost all the work, and the
+// last pivot block writes the mirror tiles (with every tile updated, 96^3 in 64
+// subdomains took 180 ms a factorisation in complex128, now 101; 160^3 in 512
+// took 224 ms in complex64, now 150).
+#include <type_traits>
+#include <utility>
+
 #include "oras_internal.h"
 
 namespace oras {
@@ -59,7 +67,9 @@ __global__ void __launch_bounds__(256) schur_T_kernel(const SubDesc* subs, int k
   if (k == 0 || k >= sd.sz) return;
   const int nt = sd.nt;
   const int I = blockIdx.y, J = blockIdx.x;
-  if (I >= nt || J >= nt) return;
+  // S_k is symmetric and only its tiles on and above the diagonal are formed:
+  // they read T up to one row of the plane below their own rows
+  if (I >= nt || J >= nt || I * TILE > J * TILE + TILE + sd.sx) return;
   const long long P2 = (long long)sd.P * sd.P;
   const T* Sinv = fac + sd.fac_off + (long long)(k - 1) * P2;
   T* Tm = tbuf + sd.t_off;
@@ -100,7 +110,8 @@ __global__ void __launch_bounds__(256) schur_T_kernel(const SubDesc* subs, int k
   }
 }
 
-// S_k = D_k - L_k T  (just D_k on the first plane), identity on the pad.
+// S_k = D_k - L_k T  (just D_k on the first plane), identity on the pad: the
+// tiles on and above the diagonal (S_k is symmetric).
 // stats[2 (sub max_sz + k)] receives the bits of max |S_k|^2 (a non-negative
 // double, so its bits order as the value).
 // The couplings of the tile's 32 rows to plane k - 1 are staged in LDS once
@@ -116,7 +127,7 @@ __global__ void __launch_bounds__(256) build_S_kernel(const SubDesc* subs, int k
   if (k >= sd.sz) return;
   const int nt = sd.nt;
   const int I = blockIdx.y, J = blockIdx.x;
-  if (I >= nt || J >= nt) return;
+  if (I > J || J >= nt) return;
   double big = 0.0;
   const long long P2 = (long long)sd.P * sd.P;
   T* S = fac + sd.fac_off + (long long)k * P2;
@@ -178,121 +189,222 @@ __global__ void __launch_bounds__(256) build_S_kernel(const SubDesc* subs, int k
 // Pivot blocks of NBT tiles (32 NBT rows); the last block of a plane may be
 // narrower.  Every pass reads and writes the whole plane matrix once, so wide
 // blocks cut the HBM traffic of the inversion; NBT is what fits the pivot
-// block in LDS for the unblocked inversion (128 x 128 FP32, 64 x 64 FP64).
+// block in LDS (128 x 128 FP32, 64 x 64 FP64).
 template <typename R> struct GjBlock;
-template <> struct GjBlock<float> { static constexpr int NBT = 4, THREADS = 1024; };
-template <> struct GjBlock<double> { static constexpr int NBT = 2, THREADS = 256; };
+template <> struct GjBlock<float> { static constexpr int NBT = 4, WAVES = 16; };
+template <> struct GjBlock<double> { static constexpr int NBT = 2, WAVES = 8; };
 
-// A_kk <- A_kk^{-1} for the pivot block (nb tiles from tile kb0) by unblocked
-// Gauss-Jordan.  The block lives in registers, a 4 x 4 sub-block per thread
-// ((NB / 4)^2 threads); each pivot step publishes the pivot row and column
-// through LDS, so a step costs two barriers.
-// stats[2 (sub max_sz + k) + 1] receives the bits of max 1 / |pivot|^2.
-template <typename R>
-__global__ void __launch_bounds__(GjBlock<R>::THREADS)
-gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
-               unsigned long long* stats, int max_sz) {
-  using T = C<R>;
-  constexpr int NB = TILE * GjBlock<R>::NBT;
-  constexpr int G = NB / 4;                  // thread grid edge
-  static_assert(G * G == GjBlock<R>::THREADS, "one 4 x 4 block per thread");
-  __shared__ T rowb[NB], colb[NB];
-  __shared__ int bad;
-  const SubDesc sd = subs[blockIdx.x];
-  if (k >= sd.sz || kb0 >= sd.nt) return;
-  const int nb = min(GjBlock<R>::NBT, sd.nt - kb0);
-  const int nr = nb * TILE;
-  T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
-  const int tr = threadIdx.x / G, tc = threadIdx.x % G;
-  const int r0 = 4 * tr, c0 = 4 * tc;
-  const bool live = r0 < nr && c0 < nr;
-  // entries (r0 + i, c0 + j): tile (r / 32, c / 32), four columns contiguous
-  T a[4][4];
-  T* blk = base + tile_off(kb0 + r0 / TILE, kb0 + c0 / TILE, sd.nt);
-  if (live) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[i][j] = blk[in_tile((r0 + i) % TILE, (c0 % TILE) + j)];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// 16 x 16 x 4 products in the precision itself: A[row = l % 16][k = l / 16],
+// B[k = l / 16][col = l % 16]; result item i of lane l is column l % 16 and row
+// l / 16 + 4 i (FP64) or 4 (l / 16) + i (FP32).
+template <typename R> struct Mma16;
+template <> struct Mma16<double> {
+  typedef f64x4 V;
+  static __device__ V mac(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-  if (threadIdx.x == 0) bad = 0;
-  R mag_min = INFINITY;    // smallest |pivot|^2 seen (thread 0)
-  for (int piv = 0; piv < nr; ++piv) {
-    const int pi = piv - r0, pj = piv - c0;
-    if (live) {
+  static __device__ int row(int kk, int i) { return kk + 4 * i; }
+};
+template <> struct Mma16<float> {
+  typedef f32x4 V;
+  static __device__ V mac(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ int row(int kk, int i) { return 4 * kk + i; }
+};
+
+// lane N of each 16 lanes, to all 16 of them (DPP row broadcast)
+template <int N> __device__ inline float row_bcast(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xf, 0xf, false));
+}
+template <int N> __device__ inline double row_bcast(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(u & 0xffffffffLL), 0x150 + N, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x150 + N, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+template <int... I, typename F>
+__device__ inline void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+// f(integral_constant<int, i>) for i = 0 .. N - 1, unrolled at compile time
+template <int N, typename F> __device__ inline void static_for(F&& f) {
+  static_for_impl(std::make_integer_sequence<int, N>(), f);
+}
+
+// A <- A^{-1} of a 16 x 16 block at m (row stride ld) by one wave: unblocked
+// Gauss-Jordan in registers, lane (r = l % 16, g = l / 16) holding row r,
+// columns 4 g .. 4 g + 3; the pivot row comes by DPP, the pivot column by a
+// lane exchange, so no pivot step waits at a barrier.  The smallest |pivot|^2
+// of the first `count` pivots goes to mag_min, a zero or non-finite one to bad.
+template <typename R>
+__device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& bad) {
+  using T = C<R>;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  T a[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (pi == i) {
+  for (int j = 0; j < 4; ++j) a[j] = m[r * ld + 4 * g + j];
+  static_for<16>([&](auto P) {
+    constexpr int piv = decltype(P)::value, pg = piv / 4, pj = piv % 4;
+    T rv[4], cv;
+    cv.x = __shfl(a[pj].x, pg * 16 + r, 64);
+    cv.y = __shfl(a[pj].y, pg * 16 + r, 64);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) rowb[c0 + j] = a[i][j];
-        }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (pj == j) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) colb[r0 + i] = a[i][j];
-        }
+    for (int j = 0; j < 4; ++j) {
+      rv[j].x = row_bcast<piv>(a[j].x);
+      rv[j].y = row_bcast<piv>(a[j].y);
     }
-    __syncthreads();
-    const T p = rowb[piv];
+    T p;
+    p.x = row_bcast<piv>(cv.x);
+    p.y = row_bcast<piv>(cv.y);
     const R mag = p.x * p.x + p.y * p.y;
     const bool ok = isfinite(p.x) && isfinite(p.y) && mag > Tiny<R>::v;
     const R inv = (R)1 / (ok ? mag : (R)1);
     T ip;
     ip.x = p.x * inv;
     ip.y = -p.y * inv;
-    if (!ok && threadIdx.x == 0) bad = 1;
-    if (ok && threadIdx.x == 0 && piv < sd.p - TILE * kb0) mag_min = fmin(mag_min, mag);
-    if (live) {
-      // every entry as if off the pivot row and column (straight-line code),
-      // then the pivot row and column rewritten from the published copies
-      T rv[4], f[4];
+    bad |= !ok;
+    if (ok && piv < count) mag_min = fmin(mag_min, mag);
+    const T f = cmul(cv, ip);                        // A_r,piv / p
 #pragma unroll
-      for (int j = 0; j < 4; ++j) rv[j] = rowb[c0 + j];
+    for (int j = 0; j < 4; ++j) {
+      T v = a[j];
+      cfms(v, f, rv[j]);
+      const T w = cmul(rv[j], ip);                   // A_piv,c / p
+      a[j].x = r == piv ? w.x : v.x;
+      a[j].y = r == piv ? w.y : v.y;
+    }
+    if (g == pg) {                                   // -A_r,piv / p
+      a[pj].x = r == piv ? ip.x : -f.x;
+      a[pj].y = r == piv ? ip.y : -f.y;
+    }
+  });
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f[i] = cmul(colb[r0 + i], ip);   // A_r,piv / p
+  for (int j = 0; j < 4; ++j) m[r * ld + 4 * g + j] = a[j];
+}
+
+// One wave's 16 x 16 block: D <- (SUB ? D : 0) -+ X Y (SUB or NEG: minus), all
+// blocks of the LDS matrix with row stride ld.  Every operand is read before
+// D is written, so D may be X or Y.
+template <typename R, bool SUB, bool NEG>
+__device__ inline void block_product(C<R>* D, const C<R>* X, const C<R>* Y, int ld) {
+  using T = C<R>;
+  using M = Mma16<R>;
+  const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
+  typename M::V re, im;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 4; ++i) {
+    T d = czero<T>();
+    if (SUB) d = D[M::row(kk, i) * ld + m];
+    re[i] = d.x;
+    im[i] = d.y;
+  }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) cfms(a[i][j], f[i], rv[j]);
+  for (int q = 0; q < 4; ++q) {
+    const T x = X[m * ld + 4 * q + kk], y = Y[(4 * q + kk) * ld + m];
+    const R xr = SUB || NEG ? -x.x : x.x, xi = SUB || NEG ? -x.y : x.y;
+    re = M::mac(xr, y.x, re);
+    im = M::mac(xr, y.y, im);
+    re = M::mac(-xi, y.y, re);
+    im = M::mac(xi, y.x, im);
+  }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (pi == i) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) a[i][j] = cmul(rv[j], ip);       // A_piv,c / p
-        }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (pj == j) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {                               // -A_r,piv / p
-            a[i][j].x = pi == i ? ip.x : -f[i].x;
-            a[i][j].y = pi == i ? ip.y : -f[i].y;
-          }
-        }
+  for (int i = 0; i < 4; ++i) {
+    T d;
+    d.x = re[i];
+    d.y = im[i];
+    D[M::row(kk, i) * ld + m] = d;
+  }
+}
+
+// A_kk <- A_kk^{-1} for the pivot block (nb tiles from tile kb0), by blocked
+// Gauss-Jordan over 16 x 16 blocks of the matrix in LDS, one work-group per
+// subdomain.  It is a chain (few work-groups, every other kernel of the plane
+// waits for it), so what counts is the length of a step: one wave inverts a
+// 16 x 16 diagonal block in registers while the others finish the previous
+// block column, and the products run on the matrix unit (64 complex FP64 rows
+// 33 us a call where 64 pivot steps with two barriers each took 75; 128 complex
+// FP32 rows on 256 subdomains 131 us against 305; 32^3 in 8 subdomains, which
+// little else but this chain keeps waiting, 12.9 -> 9.0 ms a factorisation).
+// stats[2 (sub max_sz + k) + 1] receives the bits of max 1 / |pivot|^2.
+template <typename R>
+__global__ void __launch_bounds__(64 * GjBlock<R>::WAVES)
+gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
+               unsigned long long* stats, int max_sz) {
+  using T = C<R>;
+  constexpr int NB = TILE * GjBlock<R>::NBT, LD = NB + 1, WAVES = GjBlock<R>::WAVES;
+  __shared__ __align__(16) T A[NB * LD];      // 132 KB FP32, 65 KB FP64
+  const SubDesc sd = subs[blockIdx.x];
+  if (k >= sd.sz || kb0 >= sd.nt) return;
+  const int nb = min(GjBlock<R>::NBT, sd.nt - kb0);
+  const int nblk = nb * TILE / 16;
+  T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
+  const int wv = threadIdx.x >> 6;
+  auto at = [&](int bi, int bj) { return A + 16 * (bi * LD + bj); };
+  for (int i = threadIdx.x; i < nb * nb * TILE * TILE; i += 64 * WAVES) {
+    const int t = i / (TILE * TILE), e = i % (TILE * TILE);
+    const int ti = t / nb, tj = t % nb;
+    if (ti > tj) continue;
+    const int row = ti * TILE + ((e >> 2) & 31), col = tj * TILE + (e >> 7) * 4 + (e & 3);
+    const T v = base[tile_off(kb0 + ti, kb0 + tj, sd.nt) + e];
+    A[row * LD + col] = v;
+    if (ti < tj) A[col * LD + row] = v;
+  }
+  __syncthreads();
+  R mag_min = INFINITY;    // smallest |pivot|^2 seen (wave 0)
+  bool bad = false;
+  const int live = sd.p - TILE * kb0;     // pivots that are not padding
+  for (int b = 0; b < nblk; ++b) {
+    // wave 0: the diagonal block; the rest: block column b - 1 <- -A_ik A_kk^{-1}
+    if (wv == 0) invert16<R>(at(b, b), LD, live - 16 * b, mag_min, bad);
+    else if (b > 0)
+      for (int i = wv - 1; i < nblk; i += WAVES - 1)
+        if (i != b - 1) block_product<R, false, true>(at(i, b - 1), at(i, b - 1), at(b - 1, b - 1), LD);
+    __syncthreads();
+    for (int j = wv; j < nblk; j += WAVES)
+      if (j != b) block_product<R, false, false>(at(b, j), at(b, b), at(b, j), LD);
+    __syncthreads();
+    for (int t = wv; t < (nblk - 1) * (nblk - 1); t += WAVES) {
+      int i = t / (nblk - 1), j = t % (nblk - 1);
+      i += i >= b;
+      j += j >= b;
+      block_product<R, true, false>(at(i, j), at(i, b), at(b, j), LD);
     }
     __syncthreads();
   }
+  for (int i = wv; i < nblk - 1; i += WAVES)
+    block_product<R, false, true>(at(i, nblk - 1), at(i, nblk - 1), at(nblk - 1, nblk - 1), LD);
+  __syncthreads();
+  for (int i = threadIdx.x; i < nb * nb * TILE * TILE; i += 64 * WAVES) {
+    const int t = i / (TILE * TILE), e = i % (TILE * TILE);
+    const int row = t / nb * TILE + ((e >> 2) & 31), col = t % nb * TILE + (e >> 7) * 4 + (e & 3);
+    base[tile_off(kb0 + t / nb, kb0 + t % nb, sd.nt) + e] = A[row * LD + col];
+  }
   // largest 1 / |pivot|^2 over the block's pivots
   const double inv_min = mag_min < INFINITY ? 1.0 / (double)mag_min : 0.0;
-  if (live) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) blk[in_tile((r0 + i) % TILE, (c0 % TILE) + j)] = a[i][j];
-  }
   if (threadIdx.x == 0 && bad) status[blockIdx.x] = 1;
   if (threadIdx.x == 0 && inv_min > 0.0)
     atomicMax(&stats[2 * ((long long)blockIdx.x * max_sz + k) + 1],
               (unsigned long long)__double_as_longlong(inv_min));
 }
-
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// One wave's 32 x 32 complex tile product on MFMA: acc += X Y with X and Y
-// 32 x 32 tiles in the tile layout (global or LDS).  visit(row, col, part,
-// value) walks the lane's share of the result.
+// A tile in LDS: the tile layout with each group of four columns moved on by
+// four entries, so that the lanes of a row (8 or 4 such groups) read different
+// banks.
+constexpr int LTILE = TILE / 4 * (TILE * 4 + 4);
+__device__ inline int lds_tile(int r, int c) { return (c >> 2) * (TILE * 4 + 4) + r * 4 + (c & 3); }
+// the LDS place of entry e of the tile layout
+__device__ inline int lds_entry(int e) { return e + (e >> 7) * 4; }
+
+// One wave's 32 x 32 complex tile product on MFMA: acc += X Y with X a 32 x 32
+// tile in memory (tile layout) and Y one in LDS.  visit(row, col, value)
+// walks the lane's 16 entries of the result.
 template <typename R> struct TileMma;
 
 // Complex FP32 on the bf16 instruction (32x32x16) with exactly split operands
@@ -323,7 +435,7 @@ template <> struct TileMma<float> {
 #pragma unroll
       for (int q = 0; q < 4; ++q) a[q] = X4[(4 * hj + q) * 64 + rr * 2 + g];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) y[i] = Y[in_tile(16 * hj + 4 * (i >> 1) + 2 * g + (i & 1), rr)];
+      for (int i = 0; i < 8; ++i) y[i] = Y[lds_tile(16 * hj + 4 * (i >> 1) + 2 * g + (i & 1), rr)];
       unsigned r1[4], r2[4], r3[4], i1[4], i2[4], i3[4];
       unsigned s1[4], s2[4], s3[4], t1[4], t2[4], t3[4];
 #pragma unroll
@@ -368,40 +480,40 @@ template <> struct TileMma<float> {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i / 4) + 4 * g + (i % 4);
-      f(row, rr, 0, accR[i]);
-      f(row, rr, 1, accI[i]);
+      f(row, rr, make_float2(accR[i], accI[i]));
     }
   }
 };
 
-// Complex FP64 on the 16x16x4 FP64 instruction (operands A[row = l % 16][k =
-// l / 16], B[k = l / 16][col = l % 16]; result item t of lane l is row
-// l / 16 + 4 t): two 16-row halves x four 8-column groups.
+// Complex FP64 on the 16x16x4 FP64 instruction: two 16-row halves x two
+// 16-column halves, the real and imaginary parts of the result in separate
+// accumulators.
 template <> struct TileMma<double> {
-  f64x4 acc[2][4];
+  f64x4 acc[2][2][2];
   __device__ void zero() {
 #pragma unroll
-    for (int rs = 0; rs < 2; ++rs)
-#pragma unroll
-      for (int ns = 0; ns < 4; ++ns) acc[rs][ns] = f64x4{0, 0, 0, 0};
+    for (int i = 0; i < 8; ++i) acc[i >> 2][(i >> 1) & 1][i & 1] = f64x4{0, 0, 0, 0};
   }
   __device__ void mac(const double2* __restrict__ X, const double2* __restrict__ Y) {
     const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
-    const bool odd = (m & 1) != 0;
-#pragma unroll 2
+#pragma unroll 4
     for (int q = 0; q < 8; ++q) {
-      const double2 a0 = X[(q * TILE + m) * 4 + kk];
-      const double2 a1 = X[(q * TILE + 16 + m) * 4 + kk];
-      const int kr = 4 * q + kk;
+      double2 x[2], y[2];
 #pragma unroll
-      for (int ns = 0; ns < 4; ++ns) {
-        const double2 v = Y[in_tile(kr, 8 * ns + (m >> 1))];
-        const double b1 = odd ? v.y : v.x, b2 = odd ? v.x : -v.y;
-        acc[0][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.x, b1, acc[0][ns], 0, 0, 0);
-        acc[0][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.y, b2, acc[0][ns], 0, 0, 0);
-        acc[1][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.x, b1, acc[1][ns], 0, 0, 0);
-        acc[1][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.y, b2, acc[1][ns], 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        x[h] = X[(q * TILE + 16 * h + m) * 4 + kk];
+        y[h] = Y[lds_tile(4 * q + kk, 16 * h + m)];
       }
+#pragma unroll
+      for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+        for (int ns = 0; ns < 2; ++ns) {
+          f64x4 &re = acc[rs][ns][0], &im = acc[rs][ns][1];
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].x, y[ns].x, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].x, y[ns].y, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[rs].y, y[ns].y, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].y, y[ns].x, im, 0, 0, 0);
+        }
     }
   }
   template <typename F> __device__ void visit(F f) const {
@@ -411,119 +523,127 @@ template <> struct TileMma<double> {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int ns = 0; ns < 4; ++ns)
-          f(rs * 16 + kk + 4 * t, 8 * ns + (m >> 1), m & 1, acc[rs][ns][t]);
+        for (int ns = 0; ns < 2; ++ns)
+          f(rs * 16 + kk + 4 * t, 16 * ns + m,
+            make_double2(acc[rs][ns][0][t], acc[rs][ns][1][t]));
   }
 };
 
-// component index of entry (row, col, part) of a tile
-__device__ inline int comp_of(int row, int col, int part) { return 2 * in_tile(row, col) + part; }
-
-// Copy one tile (1024 complex entries) into LDS with the wave's lanes.
-template <typename T>
-__device__ inline void tile_to_lds(const T* __restrict__ g, T* __restrict__ lds) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll 4
-  for (int i = 0; i < 1024 / 64; ++i) lds[i * 64 + lane] = g[i * 64 + lane];
-}
-
-// A_kJ <- A_kk^{-1} A_kJ for the pivot block (rows kb0 .. kb0 + nb - 1) and
-// one tile column J outside it: one work-group of NBT waves per (J, subdomain),
-// wave t producing tile (kb0 + t, J).  The nb input tiles of column J are
-// overwritten, so they are staged in LDS first.
+// The panels of one pivot block, for one tile index J outside it (one
+// work-group of NBT waves per (J, subdomain)): wave t writes
+//   C_J,t  the old A_Jk (tile t of the row, the update's left operand),
+//   W_J,t  the new A_kJ = A_kk^{-1} A_kJ (the update's right operand)
+// to the plane's scratch (C tiles of all J, then W tiles), and W_J,t to its
+// place, which for J before the pivot block is the transposed tile (J, kb0 + t).
+// The last pivot block of a plane also writes the tile's mirror.
 template <typename R>
 __global__ void __launch_bounds__(64 * GjBlock<R>::NBT)
-gj_rowpanel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac) {
+gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   using T = C<R>;
-  constexpr int NBT = GjBlock<R>::NBT;
-  __shared__ __align__(16) T sY[NBT][1024];
+  constexpr int NBT = GjBlock<R>::NBT, TT = TILE * TILE;
+  __shared__ __align__(16) T sY[NBT][LTILE];
   const SubDesc sd = subs[blockIdx.y];
   const int J = blockIdx.x;
   if (k >= sd.sz || kb0 >= sd.nt || J >= sd.nt) return;
   const int nb = min(NBT, sd.nt - kb0);
   if (J >= kb0 && J < kb0 + nb) return;
+  const bool after = J > kb0, last = kb0 + nb == sd.nt;
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
-  const int wv = threadIdx.x >> 6;
-  if (wv < nb) tile_to_lds(base + tile_off(kb0 + wv, J, sd.nt), sY[wv]);
+  T* Cs = tbuf + sd.t_off + (long long)J * NBT * TT;
+  T* Ws = Cs + (long long)sd.nt * NBT * TT;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (wv < nb) {
+    const T* g = base + (after ? tile_off(kb0 + wv, J, sd.nt) : tile_off(J, kb0 + wv, sd.nt));
+#pragma unroll 4
+    for (int i = 0; i < TT / 64; ++i) {
+      // entry e of the tile: row r, column c
+      const int e = i * 64 + lane, r = (e >> 2) & 31, c = (e >> 7) * 4 + (e & 3);
+      T v = g[e];
+      Cs[wv * TT + (after ? in_tile(c, r) : e)] = v;
+      if (!after) {        // eliminated before: A_kJ = -A_Jk^T
+        v.x = -v.x;
+        v.y = -v.y;
+      }
+      sY[wv][after ? lds_tile(r, c) : lds_tile(c, r)] = v;
+    }
+  }
   __syncthreads();
   if (wv >= nb) return;
   TileMma<R> mm;
   mm.zero();
   for (int u = 0; u < nb; ++u) mm.mac(base + tile_off(kb0 + wv, kb0 + u, sd.nt), sY[u]);
-  R* out = reinterpret_cast<R*>(base + tile_off(kb0 + wv, J, sd.nt));
-  mm.visit([&](int row, int col, int part, R v) { out[comp_of(row, col, part)] = v; });
+  T* up = base + (after ? tile_off(kb0 + wv, J, sd.nt) : tile_off(J, kb0 + wv, sd.nt));
+  T* lo = base + tile_off(kb0 + wv, J, sd.nt);     // the mirror (J before the pivot block)
+  mm.visit([&](int row, int col, T v) {
+    Ws[wv * TT + in_tile(row, col)] = v;
+    up[after ? in_tile(row, col) : in_tile(col, row)] = v;
+    if (last && !after) lo[in_tile(row, col)] = v;
+  });
 }
 
-// A_Ik <- -A_Ik A_kk^{-1} for one tile row I outside the pivot block: one
-// work-group of NBT waves per (I, subdomain), wave t producing tile (I, kb0 + t);
-// the nb input tiles of row I are staged in LDS first.
-template <typename R>
-__global__ void __launch_bounds__(64 * GjBlock<R>::NBT)
-gj_colpanel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac) {
-  using T = C<R>;
-  constexpr int NBT = GjBlock<R>::NBT;
-  __shared__ __align__(16) T sX[NBT][1024];
-  const SubDesc sd = subs[blockIdx.y];
-  const int I = blockIdx.x;
-  if (k >= sd.sz || kb0 >= sd.nt || I >= sd.nt) return;
-  const int nb = min(NBT, sd.nt - kb0);
-  if (I >= kb0 && I < kb0 + nb) return;
-  T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
-  const int wv = threadIdx.x >> 6;
-  if (wv < nb) tile_to_lds(base + tile_off(I, kb0 + wv, sd.nt), sX[wv]);
-  __syncthreads();
-  if (wv >= nb) return;
-  TileMma<R> mm;
-  mm.zero();
-  for (int u = 0; u < nb; ++u) mm.mac(sX[u], base + tile_off(kb0 + u, kb0 + wv, sd.nt));
-  R* out = reinterpret_cast<R*>(base + tile_off(I, kb0 + wv, sd.nt));
-  mm.visit([&](int row, int col, int part, R v) { out[comp_of(row, col, part)] = -v; });
-}
-
-// A_IJ <- A_IJ - A_Ik A_kJ (I, J outside the pivot block): one wave per tile.
-// For each pivot tile u the tile A_uJ is staged in LDS and A_Iu is read from
-// memory directly as the row operand; the tile A_IJ is read after the
-// products.  One 8 KB LDS tile and few live registers let five waves share a
-// SIMD (with both operands staged and A_IJ held through the loop, two).
-// Work-group ids are mapped so that all tiles of one subdomain run on the same
-// XCD and read the pivot row and column panels from its L2.
+// A_IJ <- A_IJ - C_I W_J (I <= J, both outside the pivot block): one wave per
+// tile.  For each pivot tile u the tile W_J,u is staged in LDS and C_I,u is
+// read from memory directly as the row operand; the tile A_IJ is read after
+// the products.  One LDS tile and few live registers let several waves share
+// a SIMD.  Work-group ids are mapped so that all tiles of one subdomain run on
+// the same XCD and read the panels from its L2.  The last pivot block of a
+// plane also writes the mirror tile.
 constexpr int NXCD = 8;
 template <typename R>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>* fac) {
+gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>* fac,
+                 const C<R>* tbuf) {
   using T = C<R>;
-  __shared__ __align__(16) T sY[1024];
-  const int bid = blockIdx.x, r = bid / NXCD, items = max_nt * max_nt;
+  constexpr int NBT = GjBlock<R>::NBT, TT = TILE * TILE;
+  __shared__ __align__(16) T sY[LTILE];
+  const int bid = blockIdx.x, r = bid / NXCD, items = max_nt * (max_nt + 1) / 2;
   const int sub = (r / items) * NXCD + bid % NXCD, item = r % items;
   if (sub >= nsub) return;
   const SubDesc sd = subs[sub];
-  const int I = item / max_nt, J = item % max_nt;
-  if (k >= sd.sz || kb0 >= sd.nt || I >= sd.nt || J >= sd.nt) return;
-  const int nb = min(GjBlock<R>::NBT, sd.nt - kb0);
+  // item = J (J + 1) / 2 + I
+  int J = (int)((sqrtf(8.f * item + 1.f) - 1.f) * 0.5f);
+  J += (J + 1) * (J + 2) / 2 <= item;
+  J -= J * (J + 1) / 2 > item;
+  const int I = item - J * (J + 1) / 2;
+  if (k >= sd.sz || kb0 >= sd.nt || J >= sd.nt) return;
+  const int nb = min(NBT, sd.nt - kb0);
   if ((I >= kb0 && I < kb0 + nb) || (J >= kb0 && J < kb0 + nb)) return;
+  const bool last = kb0 + nb == sd.nt;
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
-  R* Cr = reinterpret_cast<R*>(base + tile_off(I, J, sd.nt));
+  T* Aij = base + tile_off(I, J, sd.nt);
+  T* Aji = base + tile_off(J, I, sd.nt);
+  const T* Cs = tbuf + sd.t_off + (long long)I * NBT * TT;
+  const T* Ws = tbuf + sd.t_off + (long long)(sd.nt + J) * NBT * TT;
+  const int lane = threadIdx.x & 63;
   TileMma<R> mm;
   mm.zero();
   for (int u = 0; u < nb; ++u) {
-    tile_to_lds(base + tile_off(kb0 + u, J, sd.nt), sY);
+#pragma unroll 4
+    for (int i = 0; i < TT / 64; ++i) sY[lds_entry(i * 64 + lane)] = Ws[u * TT + i * 64 + lane];
     __syncthreads();
-    mm.mac(base + tile_off(I, kb0 + u, sd.nt), sY);
+    mm.mac(Cs + u * TT, sY);
     __syncthreads();
   }
-  R cv[32];
+  T cv[16];
   {
     int n = 0;
-    mm.visit([&](int row, int col, int part, R) { cv[n++] = Cr[comp_of(row, col, part)]; });
+    mm.visit([&](int row, int col, T) { cv[n++] = Aij[in_tile(row, col)]; });
   }
   int n = 0;
-  mm.visit([&](int row, int col, int part, R v) {
-    Cr[comp_of(row, col, part)] = cv[n] - v;
+  mm.visit([&](int row, int col, T v) {
+    const T w = csub(cv[n], v);
+    Aij[in_tile(row, col)] = w;
+    if (last && I != J) Aji[in_tile(col, row)] = w;
     ++n;
   });
 }
 
 }  // namespace
+
+long long factor_scratch(int factor_prec, int nt) {
+  const int nbt = factor_prec == ORAS_C64 ? GjBlock<float>::NBT : GjBlock<double>::NBT;
+  return 2LL * nt * nbt * TILE * TILE;
+}
 
 template <typename R>
 void launch_factor_plane(const SubDesc* subs_dev, int nsub, int k, int max_nt, int max_sz,
@@ -537,14 +657,13 @@ void launch_factor_plane(const SubDesc* subs_dev, int nsub, int k, int max_nt, i
   hipLaunchKernelGGL((build_S_kernel<R>), g2, dim3(256), 0, st, subs_dev, k, fac, tbuf, lca, stats,
                      max_sz);
   for (int kb0 = 0; kb0 < max_nt; kb0 += NBT) {
-    hipLaunchKernelGGL((gj_diag_kernel<R>), dim3(nsub), dim3(GjBlock<R>::THREADS), 0, st, subs_dev,
-                       k, kb0, fac, status, stats, max_sz);
-    hipLaunchKernelGGL((gj_rowpanel_kernel<R>), dim3(max_nt, nsub), dim3(64 * NBT), 0, st,
-                       subs_dev, k, kb0, fac);
-    hipLaunchKernelGGL((gj_update_kernel<R>), dim3((unsigned)(nsub8 * max_nt * max_nt)), dim3(64),
-                       0, st, subs_dev, nsub, max_nt, k, kb0, fac);
-    hipLaunchKernelGGL((gj_colpanel_kernel<R>), dim3(max_nt, nsub), dim3(64 * NBT), 0, st,
-                       subs_dev, k, kb0, fac);
+    hipLaunchKernelGGL((gj_diag_kernel<R>), dim3(nsub), dim3(64 * GjBlock<R>::WAVES),
+                       0, st, subs_dev, k, kb0, fac, status, stats, max_sz);
+    hipLaunchKernelGGL((gj_panel_kernel<R>), dim3(max_nt, nsub), dim3(64 * NBT), 0, st,
+                       subs_dev, k, kb0, fac, tbuf);
+    hipLaunchKernelGGL((gj_update_kernel<R>),
+                       dim3((unsigned)(nsub8 * (max_nt * (max_nt + 1) / 2))), dim3(64), 0, st,
+                       subs_dev, nsub, max_nt, k, kb0, fac, tbuf);
   }
 }
 

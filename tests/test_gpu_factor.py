@@ -1,0 +1,35 @@
+"""The factorisation at the edges of its tiles and pivot blocks, through the
+local solves it feeds: one subdomain, so the apply is the whole grid's inverse
+and the oracle's direct solve is its reference."""
+import numpy as np
+import pytest
+
+from oracle import oras as ooras
+from paper_2110_15113_amd import workloads as wl
+
+from gpu_util import (FP32_BOX, FP64_BOX, box_err, need_gpu, oracle_fields, rand_field, say, setup,
+                      to_dev)
+
+pytestmark = pytest.mark.gpu
+
+
+# plane sizes around whole tiles of 32 rows, pivot blocks of 2 (complex128)
+# and 4 (complex64) tiles, and 16-row blocks inside them
+@pytest.mark.parametrize("nx,ny", [(5, 3), (4, 4), (16, 2), (11, 3), (8, 8), (13, 5), (16, 6),
+                                   (97, 1 + 1), (16, 8), (43, 3), (9, 17), (32, 8), (29, 9)])
+def test_factor_edges(nx, ny):
+    need_gpu()
+    say(f"factor plane {nx}x{ny}")
+    nz = 6
+    # the grid needs 3 nodes per axis: thinner planes come from two parts along y
+    parts = (1, 1, 1) if ny >= 3 else (1, 2, 1)
+    n = (nx, ny if ny >= 3 else 4, nz)
+    w = wl.small_random(n, npml=1, q=50.0, seed=71)
+    x = rand_field((w.nz, w.ny, w.nx), 2, 72)
+    ref = ooras.ORAS(oracle_fields(w), parts, 0).apply(x)
+    for prec, bar in ((2, FP64_BOX), (1, FP32_BOX)):
+        S = setup(w, prec=prec, parts=parts, overlap=0)
+        y = S.apply_M(to_dev(x, S)).cpu().numpy()
+        e = box_err(y, ref, parts, 0)
+        say(f"  prec {prec}: {e:.2e}")
+        assert np.isfinite(e) and e < bar
