@@ -461,7 +461,7 @@ void launch_kind(const StencilMF<R>& op, const StencilTiles& tl, const X* x, con
 template <typename R>
 const StencilTiles& pick_tiles(const StencilMF<R>& op, int s) {
   for (int q = 0; q < STENCIL_LISTS - 1; ++q)
-    if ((long long)op.tl[q].ntiles * ((s + 15) / 16) >= 512) return op.tl[q];
+    if ((long long)op.tl[q].ntiles * ((s + 15) / 16) >= STENCIL_ITEMS) return op.tl[q];
   return op.tl[STENCIL_LISTS - 1];
 }
 

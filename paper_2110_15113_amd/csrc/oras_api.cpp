@@ -324,6 +324,7 @@ oras_status build_fields(oras_ctx c) {
     c->mf_first[q] = (int)(tiles.size() / 4);
     c->mf_ntiles[q] = (int)(list.size() / 4);
     tiles.insert(tiles.end(), list.begin(), list.end());
+    if (c->mf_ntiles[q] >= STENCIL_ITEMS) break;   // lower tiles are never taken
   }
   TRY(dev_alloc(c, c->mftiles, tiles.size() * sizeof(int)));
   HIP_TRY(c, hipMemcpyAsync(c->mftiles.p, tiles.data(), tiles.size() * sizeof(int),
