@@ -206,21 +206,26 @@ plane_rhs_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int nrb, int ncc
   out[128] = u32x4{p3[0], p3[1], p3[2], p3[3]};
 }
 
-// Y_k (=|-=) S_k^{-1} t for RT 32-row tiles and one 32-column chunk (one
-// wave), on the bf16 instruction with split operands.  The real and imaginary
+// Y_k (=|-=) S_k^{-1} t for RT 32-row tiles and one 32-column chunk per
+// work-group of KS waves, each taking a KS-th of the k range (in half tiles of
+// 16 k), on the bf16 instruction with split operands.  The real and imaginary
 // parts of the result are separate accumulators:
 //   Re += Ar Br - Ai Bi,  Im += Ar Bi + Ai Br,
 // six piece products each, 24 instructions per 16 k and row tile; the RT row
 // tiles share every t piece the wave loads.  The next half tile of the factor
 // rows and of the t pieces is fetched while the current one feeds the
-// products; the factor rows are streamed once (non-temporal loads).
-template <typename Z, int RT>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 3 : 2)))
+// products; the factor rows are streamed once (non-temporal loads).  The
+// waves' sums meet in LDS and each wave adds up and stores a KS-th of the rows.
+// Large launches are bound by the factor stream (4.6 TB/s on 160^3, 32
+// right-hand sides, of 5.1 for a large copy).
+template <typename Z, int RT, int KS>
+__global__ void __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 3 : 2)))
 plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int ncc, int k,
                      int bwd, const float2* __restrict__ fac, const u32x4* __restrict__ tp,
                      float2* __restrict__ ybuf, Z* __restrict__ z, int nx, int ny, int s,
                      int s32) {
   using ZR = typename Comp<Z>::type;
+  __shared__ float red[KS][RT * 32][64];
   int sub, item;
   xcd_map(max_ng * ncc, sub, item);
   if (sub >= nsub) return;
@@ -236,7 +241,8 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
     A4[t] = reinterpret_cast<const float4*>(fac + sd.fac_off + (long long)k * P * P) +
             (long long)min(I0 + t, nt - 1) * nt * 512;
   const u32x4* B = tp + sd.tv_off * s32 * 3 / 4 + (long long)cc * (P / 16) * 6 * 64;
-  const int lane = threadIdx.x, rr = lane & 31, g = lane >> 5;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rr = lane & 31, g = lane >> 5;
   const int aoff = rr * 2 + g;
 
   f32x16 accR[RT], accI[RT];
@@ -247,16 +253,20 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
       accR[t][j] = 0.f;
       accI[t][j] = 0.f;
     }
+  // the wave's half tiles [h0, h1)
+  const int h0 = 2 * nt * wv / KS, h1 = 2 * nt * (wv + 1) / KS;
   float4 sa[RT][4];
   u32x4 sb[6];
+  if (h0 < h1) {
 #pragma unroll
-  for (int t = 0; t < RT; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sa[t][q] = ld_nt(&A4[t][q * 64 + aoff]);
+      for (int q = 0; q < 4; ++q) sa[t][q] = ld_nt(&A4[t][h0 * 256 + q * 64 + aoff]);
 #pragma unroll
-  for (int pi = 0; pi < 6; ++pi) sb[pi] = B[pi * 64 + lane];
+    for (int pi = 0; pi < 6; ++pi) sb[pi] = B[(h0 * 6 + pi) * 64 + lane];
+  }
 
-  for (int HJ = 0; HJ < 2 * nt; ++HJ) {
+  for (int HJ = h0; HJ < h1; ++HJ) {
     float4 ca[RT][4];
     u32x4 cb[6];
 #pragma unroll
@@ -265,13 +275,13 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
       for (int q = 0; q < 4; ++q) ca[t][q] = sa[t][q];
 #pragma unroll
     for (int pi = 0; pi < 6; ++pi) cb[pi] = sb[pi];
-    if (HJ + 1 < 2 * nt) {
-      const int J1 = (HJ + 1) >> 1, h1 = (HJ + 1) & 1;
+    if (HJ + 1 < h1) {
+      const int J1 = (HJ + 1) >> 1, h = (HJ + 1) & 1;
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          sa[t][q] = ld_nt(&A4[t][(long long)J1 * 512 + (4 * h1 + q) * 64 + aoff]);
+          sa[t][q] = ld_nt(&A4[t][(long long)J1 * 512 + (4 * h + q) * 64 + aoff]);
 #pragma unroll
       for (int pi = 0; pi < 6; ++pi) sb[pi] = B[((long long)(HJ + 1) * 6 + pi) * 64 + lane];
     }
@@ -296,10 +306,10 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
       const bf16x8 Ni1 = as_bf16x8(u32x4{i1[0], i1[1], i1[2], i1[3]} ^ sgn);
       const bf16x8 Ni2 = as_bf16x8(u32x4{i2[0], i2[1], i2[2], i2[3]} ^ sgn);
       const bf16x8 Ni3 = as_bf16x8(u32x4{i3[0], i3[1], i3[2], i3[3]} ^ sgn);
-#define ORAS_X3(AR, AI, NI, BR, BI)                                                \
+#define ORAS_X3(AR, AI, NI_, BR, BI)                                               \
   accR[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AR, BR, accR[t], 0, 0, 0);     \
   accI[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AR, BI, accI[t], 0, 0, 0);     \
-  accR[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(NI, BI, accR[t], 0, 0, 0);     \
+  accR[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(NI_, BI, accR[t], 0, 0, 0);    \
   accI[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AI, BR, accI[t], 0, 0, 0);
       ORAS_X3(Ar1, Ai1, Ni1, Br1, Bi1)
       ORAS_X3(Ar1, Ai1, Ni1, Br2, Bi2)
@@ -312,6 +322,18 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
   }
 
   // accumulator item i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
+  constexpr int NI = 16 / KS;      // items per wave and row tile
+  static_assert(KS > 1 && NI * KS == 16, "whole items per wave");
+  {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        red[wv][t * 32 + i][lane] = accR[t][i];
+        red[wv][t * 32 + 16 + i][lane] = accI[t][i];
+      }
+    __syncthreads();
+  }
   const bool final_plane = bwd || (k == sd.sz - 1);
   const int col = 32 * cc + rr;
   float2* Yk = ybuf + (sd.y_off + (long long)k * P) * s;
@@ -321,22 +343,27 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
     const int I = I0 + t;
     if (I >= nt) break;
     // backward: read every old value first (all loads in flight together)
-    float2 old[16];
+    float2 old[NI], sum[NI];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) old[i] = make_float2(0.f, 0.f);
-    if (bwd) {
+    for (int j = 0; j < NI; ++j) {
+      const int i = NI * wv + j, row = I * TILE + 8 * (i / 4) + 4 * g + (i % 4);
+      old[j] = bwd ? Yk[(long long)row * s + colc] : make_float2(0.f, 0.f);
+    }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int row = I * TILE + 8 * (i / 4) + 4 * g + (i % 4);
-        old[i] = Yk[(long long)row * s + colc];
+    for (int j = 0; j < NI; ++j) {
+      sum[j] = make_float2(red[0][t * 32 + NI * wv + j][lane], red[0][t * 32 + 16 + NI * wv + j][lane]);
+#pragma unroll
+      for (int w = 1; w < KS; ++w) {
+        sum[j].x += red[w][t * 32 + NI * wv + j][lane];
+        sum[j].y += red[w][t * 32 + 16 + NI * wv + j][lane];
       }
     }
     if (col >= s) continue;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = I * TILE + 8 * (i / 4) + 4 * g + (i % 4);
-      float2 val = make_float2(accR[t][i], accI[t][i]);
-      if (bwd) val = make_float2(old[i].x - val.x, old[i].y - val.y);
+    for (int j = 0; j < NI; ++j) {
+      const int i = NI * wv + j, row = I * TILE + 8 * (i / 4) + 4 * g + (i % 4);
+      float2 val = sum[j];
+      if (bwd) val = make_float2(old[j].x - val.x, old[j].y - val.y);
       Yk[(long long)row * s + col] = val;
       if (final_plane && row < sd.p) {
         const int qx = row % sd.sx, qy = row / sd.sx;
@@ -422,7 +449,10 @@ plane_rhs_f64_kernel(const SubDesc* __restrict__ subs, int k, int bwd,
 
 // 16-byte loads through a buffer descriptor over an operand that starts at a
 // wave-uniform address (byte offsets: vo per lane, so per wave; every operand
-// is far below 2 GB).  NT = 2 marks a streamed operand non-temporal.
+// is far below 2 GB).  They keep the order the program gives them; ordinary
+// loads at the end of an iteration are moved to the head of the next one, where
+// their whole latency is waited for.  NT = 2 marks a streamed operand
+// non-temporal.
 typedef __amdgpu_buffer_rsrc_t BufRsrc;
 __device__ inline BufRsrc buf_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00027000);
@@ -473,9 +503,7 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
   const int m = lane & 15, kk = lane >> 4;
   const bool im = (m & 1) != 0;
   // k-step g (4 columns) of the row tile starts at entry 128 g, its upper 16
-  // rows at + 64; buffer loads keep the order written here (ordinary loads at
-  // the end of an iteration are moved to the head of the next one, where
-  // their whole latency is waited for)
+  // rows at + 64
   const BufRsrc A = buf_rsrc(fac + sd.fac_off + (long long)k * P * P +
                              (long long)(row0 / TILE) * nt * (TILE * TILE) + (row0 % TILE) * 4);
   const BufRsrc B = buf_rsrc(tvbuf + sd.tv_off * pad16(s) + c0);
@@ -659,13 +687,20 @@ void plane_step_f32(const OrasPlan& pl, int k, int bwd, const float2* fac, const
                      st, pl.subs, pl.nsub, nrb, ncc, k, bwd, lca, ybuf, tp, v, scale, nx, ny, s,
                      s32);
   if (ev) (void)hipEventRecord(ev[0], st);
-  // two row tiles per wave share each t piece they load: 278.8 -> 265.6 us
-  // per plane step on 160^3, 32 RHS (212 registers, two waves per SIMD)
-  constexpr int RT = 2;
-  const int max_ng = (pl.max_nt + RT - 1) / RT;
-  hipLaunchKernelGGL((plane_gemm_x3_kernel<Z, RT>), dim3((unsigned)(nsub8 * max_ng * ncc)),
-                     dim3(64), 0, st, pl.subs, pl.nsub, max_ng, ncc, k, bwd, fac, tp, ybuf, z, nx,
-                     ny, s, s32);
+  // Two row tiles per work-group share each t piece they load, which pays
+  // while there are work-groups to spare; the k range goes over four waves
+  // either way (measured per plane step, with one wave and two row tiles in
+  // brackets: two tiles 295 (302) us on 160^3 in 512 subdomains, 128 (129) on
+  // 120^3 in 216, 78 (82) on 96^3 in 64; one tile 311, 132, 75, and on
+  // 61 x 47 x 53 in 18 subdomains 26 (49), on 32^3 in 8 11 (30)).
+  auto gemm = [&](auto rt) {
+    const int max_ng = (pl.max_nt + rt() - 1) / rt();
+    hipLaunchKernelGGL((plane_gemm_x3_kernel<Z, rt(), 4>), dim3((unsigned)(nsub8 * max_ng * ncc)),
+                       dim3(256), 0, st, pl.subs, pl.nsub, max_ng, ncc, k, bwd, fac, tp, ybuf, z,
+                       nx, ny, s, s32);
+  };
+  if ((long long)nsub8 * pl.max_nt * ncc >= 2048) gemm(std::integral_constant<int, 2>());
+  else gemm(std::integral_constant<int, 1>());
   if (ev) (void)hipEventRecord(ev[1], st);
 }
 

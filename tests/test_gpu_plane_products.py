@@ -7,7 +7,8 @@ import pytest
 from oracle import oras as ooras
 from paper_2110_15113_amd import workloads as wl
 
-from gpu_util import (FP64_BOX, box_err, need_gpu, oracle_fields, rand_field, say, setup, to_dev)
+from gpu_util import (FP32_BOX, FP64_BOX, box_err, need_gpu, oracle_fields, rand_field, say, setup,
+                      to_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +37,16 @@ def test_plane_products_c128(grid, nrhs):
     S = setup(w, prec=2, parts=c["parts"], overlap=c["ov"])
     y = S.apply_M(to_dev(x[:nrhs], S)).cpu().numpy()
     assert box_err(y, ref[:nrhs], c["parts"], c["ov"]) < FP64_BOX
+
+
+# one, two chunks of 32 columns, the last one partial
+@pytest.mark.parametrize("nrhs", [1, 32, 47])
+@pytest.mark.parametrize("grid", list(GRIDS))
+def test_plane_products_c64(grid, nrhs):
+    need_gpu()
+    say(f"plane products c64 {grid} nrhs={nrhs}")
+    c = GRIDS[grid]
+    w, x, ref = reference(grid)
+    S = setup(w, prec=1, parts=c["parts"], overlap=c["ov"])
+    y = S.apply_M(to_dev(x[:nrhs], S)).cpu().numpy()
+    assert box_err(y, ref[:nrhs], c["parts"], c["ov"]) < FP32_BOX
