@@ -402,22 +402,24 @@ __device__ inline bool item_map(int nitems, int ncg, int& it, int& cg) {
 // Complex FP32 on the bf16 instruction (32x32x16) with exactly split operands,
 // as the dense plane products: every FP32 value of both operands is split
 // into three bf16 pieces and six piece products form each real product, so
-// each product carries an FP32-level error and accumulates in FP32.  One
-// wave takes 32 rows and one 32-column chunk; the real and imaginary parts
-// are separate accumulators.  A 16-k step covers four 4-row groups of the
+// each product carries an FP32-level error and accumulates in FP32.  A
+// work-group of KS waves takes 32 rows and one 32-column chunk, each wave a
+// KS-th of the operand's columns; the real and imaginary parts are separate
+// accumulators.  A 16-k step covers four 4-row groups of the
 // stored operand: lane (n = lane % 32, g = lane / 32) holds the operand
 // entries (row n, k = 4 q + 2 g + e) and the t or T values (k = 4 q + 2 g + e,
 // column n), value i = 2 q + e of both instruction operands referring to the
 // same k.  A run of 4 m + 2 groups ends with a step whose last two groups are
 // zeroed in the stored operand.
-template <int MODE, typename Z>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+template <int MODE, int KS, typename Z>
+__global__ void __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(2)))
 blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ bsubs,
                    const BlrItem* __restrict__ items, int nitems, int ncg, int k, int bwd,
                    const float2* __restrict__ astore, const int* __restrict__ lists,
                    float2* __restrict__ bt, float2* __restrict__ ybuf, Z* __restrict__ z,
                    int nx, int ny, int s, int s16) {
   using ZR = typename std::conditional<sizeof(Z) == 8, float, double>::type;
+  __shared__ float red[KS > 1 ? KS : 1][KS > 1 ? 32 : 1][64];
   int it, cg;
   if (!item_map(nitems, ncg, it, cg)) return;
   const BlrItem item = items[it];
@@ -427,7 +429,8 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
   const BlrSub bs = bsubs[item.sub];
   const float2* btc = bt + bs.bt_off * s16;
   const float4* A = reinterpret_cast<const float4*>(astore + item.a_off);
-  const int lane = threadIdx.x, n = lane & 31, g = lane >> 5;
+  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5;
+  const int wv = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // columns at or beyond s16 read column s16 - 1 (in bounds; their results are dropped)
   const int colb = min(32 * cg + n, s16 - 1);
   f32x16 accR, accI;
@@ -506,26 +509,58 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
       mma(ca, cb);
     }
   };
+  // the wave's part of a run: groups [w0, w1) of the operand's K / 4
+  const int w0 = 2 * (item.K / 8 * wv / KS), w1 = 2 * (item.K / 8 * (wv + 1) / KS);
+  auto share = [&](int q0, int q1, int rbase0) {
+    const int a = max(q0, w0), b = min(q1, w1);
+    if (a < b) run(a, b, rbase0 + 4 * (a - q0));
+  };
   if (MODE == 0) {
-    run(0, item.K >> 2, item.brow);
+    share(0, item.K >> 2, item.brow);
   } else {
     for (int sg = 0; sg < item.nseg; ++sg) {
       const int4 seg = *reinterpret_cast<const int4*>(lists + item.list_off + 4 * sg);
-      run(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
+      share(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
     }
   }
+  // the waves' sums in order; each wave adds up and stores NI of the 16 items.
   // accumulator item i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
+  constexpr int NI = 16 / KS;
+  float2 sum[NI];
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) sum[j] = make_float2(accR[j], accI[j]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      red[wv][i][lane] = accR[i];
+      red[wv][16 + i][lane] = accI[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      sum[j] = make_float2(red[0][NI * wv + j][lane], red[0][16 + NI * wv + j][lane]);
+#pragma unroll
+      for (int w = 1; w < KS; ++w) {
+        sum[j].x += red[w][NI * wv + j][lane];
+        sum[j].y += red[w][16 + NI * wv + j][lane];
+      }
+    }
+  }
+  auto row_of = [&](int j) {
+    const int i = NI * wv + j;
+    return 8 * (i / 4) + 4 * g + (i % 4);
+  };
   const int col = 32 * cg + n;
   if (MODE == 0) {
     // destination rows first (all loads in flight together), then the stores
-    int dest[16];
+    int dest[NI];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dest[i] = lists[item.list_off + 8 * (i / 4) + 4 * g + (i % 4)];
+    for (int j = 0; j < NI; ++j) dest[j] = lists[item.list_off + row_of(j)];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int lr = 8 * (i / 4) + 4 * g + (i % 4);
-      if (lr >= item.rows || col >= s) continue;
-      bt[(bs.bt_off + dest[i]) * s16 + col] = make_float2(accR[i], accI[i]);
+    for (int j = 0; j < NI; ++j) {
+      if (row_of(j) >= item.rows || col >= s) continue;
+      bt[(bs.bt_off + dest[j]) * s16 + col] = sum[j];
     }
     return;
   }
@@ -537,23 +572,23 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
   const int colc = min(col, s - 1);
   // backward: x_k = y_k - (...): read every old value first (all loads in
   // flight together), then write
-  float2 old[16];
+  float2 old[NI];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) old[i] = make_float2(0.f, 0.f);
+  for (int j = 0; j < NI; ++j) old[j] = make_float2(0.f, 0.f);
   if (bwd) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int l = min(item.row0 + 8 * (i / 4) + 4 * g + (i % 4), bsz - 1);
-      old[i] = Yk[(long long)((y0 + l / w) * sd.sx + x0 + l % w) * s + colc];
+    for (int j = 0; j < NI; ++j) {
+      const int l = min(item.row0 + row_of(j), bsz - 1);
+      old[j] = Yk[(long long)((y0 + l / w) * sd.sx + x0 + l % w) * s + colc];
     }
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int l = item.row0 + 8 * (i / 4) + 4 * g + (i % 4);
+  for (int j = 0; j < NI; ++j) {
+    const int l = item.row0 + row_of(j);
     if (l >= bsz || col >= s) continue;
     const int qx = x0 + l % w, qy = y0 + l / w;
-    float2 val = make_float2(accR[i], accI[i]);
-    if (bwd) val = make_float2(old[i].x - val.x, old[i].y - val.y);
+    float2 val = sum[j];
+    if (bwd) val = make_float2(old[j].x - val.x, old[j].y - val.y);
     Yk[(long long)(qy * sd.sx + qx) * s + col] = val;
     if (final_plane) {
       const int gx = sd.lo[0] + qx, gy = sd.lo[1] + qy, gz = sd.lo[2] + k;
@@ -567,16 +602,21 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
   }
 }
 
-// Complex FP64: 16x16x4 MFMA, RG groups of 16 rows x 16 columns per wave.
+// Complex FP64: 16x16x4 MFMA, 32 rows x NB blocks of 16 columns per work-group
+// of KS waves, each taking a KS-th of the operand's columns; the real and
+// imaginary parts of the result are separate accumulators.  The waves' sums
+// meet in LDS and each wave adds up and stores its share.
 // A[row = lane % 16][k = lane / 16], B[k = lane / 16][col = lane % 16];
 // result item t of lane l is row l / 16 + 4 t, column l % 16.
-template <int RG, int MODE>
-__global__ void __launch_bounds__(64)
+template <int MODE, int KS, int NB>
+__global__ void __launch_bounds__(64 * KS)
 blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ bsubs,
                     const BlrItem* __restrict__ items, int nitems, int ncg, int k, int bwd,
                     const double2* __restrict__ astore, const int* __restrict__ lists,
                     double2* __restrict__ bt, double2* __restrict__ ybuf,
                     double2* __restrict__ z, int nx, int ny, int s, int s16) {
+  constexpr int RG = 2, NE = RG * NB * 4;      // 16-row groups; result items per lane
+  __shared__ double2 red[KS][KS > 1 ? NE : 1][64];
   int it, cg;
   if (!item_map(nitems, ncg, it, cg)) return;
   const BlrItem item = items[it];
@@ -586,45 +626,43 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
   const BlrSub bs = bsubs[item.sub];
   const double2* btc = bt + bs.bt_off * s16;
   const double2* A = astore + item.a_off;
-  const int lane = threadIdx.x, m = lane & 15, kk = lane >> 4;
-  const int bn = m >> 1;
-  const bool im = (m & 1) != 0;
-  const int c0 = 16 * cg;
+  const int wv = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
+  const int c0 = 16 * NB * cg;
   // columns at or beyond s16 read column s16 - 1 (in bounds; their results are dropped)
-  int colc[2];
+  int colc[NB];
 #pragma unroll
-  for (int ns = 0; ns < 2; ++ns) colc[ns] = min(c0 + 8 * ns + bn, s16 - 1);
-  f64x4 acc[RG][2];
+  for (int nb = 0; nb < NB; ++nb) colc[nb] = min(c0 + 16 * nb + m, s16 - 1);
+  f64x4 acc[RG][NB][2];
 #pragma unroll
-  for (int rg = 0; rg < RG; ++rg)
-#pragma unroll
-    for (int ns = 0; ns < 2; ++ns) acc[rg][ns] = f64x4{0, 0, 0, 0};
+  for (int q = 0; q < RG * NB * 2; ++q)
+    acc[q / (2 * NB)][(q >> 1) % NB][q & 1] = f64x4{0, 0, 0, 0};
   // one 4-row group: lane kk takes operand row 4 kq + kk
-  auto load = [&](int kq, int rbase, double2 (&bv)[2], double2 (&a)[RG]) {
+  auto load = [&](int kq, int rbase, double2 (&bv)[NB], double2 (&a)[RG]) {
     const long long row = rbase + kk;
 #pragma unroll
-    for (int ns = 0; ns < 2; ++ns) bv[ns] = btc[row * s16 + colc[ns]];
+    for (int nb = 0; nb < NB; ++nb) bv[nb] = btc[row * s16 + colc[nb]];
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg)
       a[rg] = A[((long long)kq * item.mpad + item.row0 + 16 * rg + m) * 4 + kk];
   };
-  auto mma = [&](const double2 (&bv)[2], const double2 (&a)[RG]) {
+  auto mma = [&](const double2 (&bv)[NB], const double2 (&a)[RG]) {
 #pragma unroll
-    for (int ns = 0; ns < 2; ++ns) {
-      const double b1 = im ? bv[ns].y : bv[ns].x;
-      const double b2 = im ? bv[ns].x : -bv[ns].y;
+    for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
-      for (int rg = 0; rg < RG; ++rg) {
-        acc[rg][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, b1, acc[rg][ns], 0, 0, 0);
-        acc[rg][ns] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].y, b2, acc[rg][ns], 0, 0, 0);
+      for (int nb = 0; nb < NB; ++nb) {
+        f64x4 &re = acc[rg][nb][0], &im = acc[rg][nb][1];
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv[nb].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv[nb].y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[rg].y, bv[nb].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].y, bv[nb].x, im, 0, 0, 0);
       }
-    }
   };
-  // two groups in flight in two register sets, as in the FP32 kernel (runs
-  // are multiples of 8 rows: an even number of groups; nothing conditional)
+  // two groups in flight in two register sets (runs are multiples of 8 rows:
+  // an even number of groups; nothing conditional)
   auto run = [&](int q0, int q1, int rbase0) {
-    double2 b0[2], b1[2], a0[RG], a1[RG];
-    auto ld = [&](int kq, double2 (&bv)[2], double2 (&a)[RG]) {
+    double2 b0[NB], b1[NB], a0[RG], a1[RG];
+    auto ld = [&](int kq, double2 (&bv)[NB], double2 (&a)[RG]) {
       const int g = min(kq, q1 - 1);
       load(g, rbase0 + 4 * (g - q0), bv, a);
     };
@@ -642,63 +680,74 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  // the wave's part of a run: groups [w0, w1) of the operand's K / 4, in pairs
+  const int w0 = 2 * (item.K / 8 * wv / KS), w1 = 2 * (item.K / 8 * (wv + 1) / KS);
+  auto share = [&](int q0, int q1, int rbase0) {
+    const int a = max(q0, w0), b = min(q1, w1);
+    if (a < b) run(a, b, rbase0 + 4 * (a - q0));
+  };
   if (MODE == 0) {
-    run(0, item.K >> 2, item.brow);
+    share(0, item.K >> 2, item.brow);
   } else {
     for (int sg = 0; sg < item.nseg; ++sg) {
       const int4 seg = *reinterpret_cast<const int4*>(lists + item.list_off + 4 * sg);
-      run(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
+      share(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
     }
   }
-  if (MODE == 0) {
+  // result item e of a lane: row group e / (4 NB), column block (e / 4) % NB, t = e % 4
+  auto own = [&](int e) {
+    return make_double2(acc[e / (4 * NB)][(e >> 2) % NB][0][e & 3],
+                        acc[e / (4 * NB)][(e >> 2) % NB][1][e & 3]);
+  };
+  if (KS > 1) {
 #pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int lr = 16 * rg + kk + 4 * t;
-        if (lr >= item.rows) continue;
-        double* Tf = reinterpret_cast<double*>(bt + (bs.bt_off + lists[item.list_off + lr]) * s16);
-#pragma unroll
-        for (int ns = 0; ns < 2; ++ns) {
-          const int col = c0 + 8 * ns + bn;
-          if (col >= s) continue;
-          Tf[2 * col + (im ? 1 : 0)] = acc[rg][ns][t];
-        }
-      }
-    return;
+    for (int e = 0; e < NE; ++e) red[wv][KS > 1 ? e : 0][lane] = own(e);
+    __syncthreads();
   }
-  int x0, w, y0, hh;
-  patch_box(sd.sx, sd.sy, bs.npx, bs.npy, item.patch, x0, w, y0, hh);
+  int x0 = 0, w = 1, y0 = 0, hh = 0;
+  if (MODE == 1) patch_box(sd.sx, sd.sy, bs.npx, bs.npy, item.patch, x0, w, y0, hh);
   const int bsz = w * hh;
   const bool final_plane = bwd || (k == sd.sz - 1);
-  double* Yk = reinterpret_cast<double*>(ybuf + (sd.y_off + (long long)k * sd.P) * s);
+  double2* Yk = ybuf + (sd.y_off + (long long)k * sd.P) * s;
 #pragma unroll
-  for (int rg = 0; rg < RG; ++rg)
+  for (int j = 0; j < NE / KS; ++j) {
+    const int e = NE / KS * wv + j;
+    const int lr = 16 * (e / (4 * NB)) + kk + 4 * (e & 3), col = c0 + 16 * ((e >> 2) % NB) + m;
+    if (col >= s) continue;
+    double2 val;
+    if constexpr (KS == 1) {
+      val = own(j);
+    } else {
+      val = red[0][e][lane];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int l = item.row0 + 16 * rg + kk + 4 * t;
-      if (l >= bsz) continue;
-      const int qx = x0 + l % w, qy = y0 + l / w;
-      double* yr = Yk + (long long)(qy * sd.sx + qx) * 2 * s;
-      long long zoff = -1;
-      if (final_plane) {
-        const int gx = sd.lo[0] + qx, gy = sd.lo[1] + qy, gz = sd.lo[2] + k;
-        if (gx >= sd.olo[0] && gx < sd.ohi[0] && gy >= sd.olo[1] && gy < sd.ohi[1] &&
-            gz >= sd.olo[2] && gz < sd.ohi[2])
-          zoff = (((long long)gz * ny + gy) * nx + gx) * s;
-      }
-#pragma unroll
-      for (int ns = 0; ns < 2; ++ns) {
-        const int col = c0 + 8 * ns + bn;
-        if (col >= s) continue;
-        const int fi = 2 * col + (im ? 1 : 0);
-        double val = acc[rg][ns][t];
-        if (bwd) val = yr[fi] - val;
-        yr[fi] = val;
-        if (zoff >= 0) reinterpret_cast<double*>(z + zoff)[fi] = val;
-      }
+      for (int u = 1; u < KS; ++u) val = cadd(val, red[u][e][lane]);
     }
+    if (MODE == 0) {
+      if (lr < item.rows) bt[(bs.bt_off + lists[item.list_off + lr]) * s16 + col] = val;
+      continue;
+    }
+    const int l = item.row0 + lr;
+    if (l >= bsz) continue;
+    const int qx = x0 + l % w, qy = y0 + l / w;
+    double2* yr = Yk + (long long)(qy * sd.sx + qx) * s + col;
+    if (bwd) val = csub(*yr, val);
+    *yr = val;
+    if (final_plane) {
+      const int gx = sd.lo[0] + qx, gy = sd.lo[1] + qy, gz = sd.lo[2] + k;
+      if (gx >= sd.olo[0] && gx < sd.ohi[0] && gy >= sd.olo[1] && gy < sd.ohi[1] &&
+          gz >= sd.olo[2] && gz < sd.ohi[2])
+        z[(((long long)gz * ny + gy) * nx + gx) * s + col] = val;
+    }
+  }
 }
+
+// Waves per work-group of a launch: four where the items are few, so that the
+// chip is not waiting for single waves' chains (per plane step, projection and
+// expansion, one wave in brackets: complex64 32^3 in 8 subdomains 14.7 (21.7)
+// us, 61 x 47 x 53 in 18 22.6 (27.7); complex128 15.1 (24.2) and 23.8 (33.6)); one
+// where there are enough (complex64 96^3 in 64 47.6 against 59.2, 160^3 in 512
+// 159 against 208; complex128 96^3 82.7 against 84.3).
+inline bool split_items(int count, int ncg) { return (long long)count * ncg < 1024; }
 
 template <typename R, typename Z> struct BlrStep;
 template <typename Z> struct BlrStep<float, Z> {
@@ -712,14 +761,18 @@ template <typename Z> struct BlrStep<float, Z> {
                        ybuf, bt, v, scale, nx, ny, s, s16);
     if (ev) (void)hipEventRecord(ev[0], st);
     const int ncg = (s + 31) / 32;
-    if (pl.p_count[k] > 0)
-      hipLaunchKernelGGL((blr_gemm_x3_kernel<0, Z>), dim3((unsigned)(pl.p_count[k] * ncg)),
-                         dim3(64), 0, st, pl.subs, pl.bsubs, pl.items + pl.p_first[k],
-                         pl.p_count[k], ncg, k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s,
-                         s16);
-    hipLaunchKernelGGL((blr_gemm_x3_kernel<1, Z>), dim3((unsigned)(pl.e_count[k] * ncg)),
-                       dim3(64), 0, st, pl.subs, pl.bsubs, pl.items + pl.e_first[k],
-                       pl.e_count[k], ncg, k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s, s16);
+    auto gemm = [&](auto mode, int first, int count) {
+      if (count == 0) return;
+      auto launch = [&](auto ks) {
+        hipLaunchKernelGGL((blr_gemm_x3_kernel<mode(), ks(), Z>), dim3((unsigned)(count * ncg)),
+                           dim3(64 * ks()), 0, st, pl.subs, pl.bsubs, pl.items + first, count, ncg,
+                           k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s, s16);
+      };
+      if (split_items(count, ncg)) launch(std::integral_constant<int, 4>());
+      else launch(std::integral_constant<int, 1>());
+    };
+    gemm(std::integral_constant<int, 0>(), pl.p_first[k], pl.p_count[k]);
+    gemm(std::integral_constant<int, 1>(), pl.e_first[k], pl.e_count[k]);
     if (ev) (void)hipEventRecord(ev[1], st);
   }
 };
@@ -733,15 +786,31 @@ template <> struct BlrStep<double, double2> {
                        0, st, pl.subs, pl.bsubs, pl.lists, k, bwd, lca, ybuf, bt, v, scale, nx, ny,
                        s, s16);
     if (ev) (void)hipEventRecord(ev[0], st);
-    const int ncg = (s + 15) / 16;
-    if (pl.p_count[k] > 0)
-      hipLaunchKernelGGL((blr_gemm_f64_kernel<2, 0>), dim3((unsigned)(pl.p_count[k] * ncg)),
-                         dim3(64), 0, st, pl.subs, pl.bsubs, pl.items + pl.p_first[k],
-                         pl.p_count[k], ncg, k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s,
-                         s16);
-    hipLaunchKernelGGL((blr_gemm_f64_kernel<2, 1>), dim3((unsigned)(pl.e_count[k] * ncg)),
-                       dim3(64), 0, st, pl.subs, pl.bsubs, pl.items + pl.e_first[k],
-                       pl.e_count[k], ncg, k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s, s16);
+    // one block of 16 columns per work-group, two where there are two: the
+    // operand is then read once for both
+    const bool two = s > 16;
+    const int ncg = two ? (s + 31) / 32 : 1;
+    auto gemm = [&](auto mode, int first, int count) {
+      if (count == 0) return;
+      auto launch = [&](auto ks, auto nb) {
+        hipLaunchKernelGGL((blr_gemm_f64_kernel<mode(), ks(), nb()>),
+                           dim3((unsigned)(count * ncg)), dim3(64 * ks()), 0, st, pl.subs,
+                           pl.bsubs, pl.items + first, count, ncg, k, bwd, astore, pl.lists, bt,
+                           ybuf, z, nx, ny, s, s16);
+      };
+      const std::integral_constant<int, 1> n1;
+      const std::integral_constant<int, 2> n2;
+      const std::integral_constant<int, 4> n4;
+      if (split_items(count, ncg)) {
+        if (two) launch(n4, n2);
+        else launch(n4, n1);
+      } else {
+        if (two) launch(n1, n2);
+        else launch(n1, n1);
+      }
+    };
+    gemm(std::integral_constant<int, 0>(), pl.p_first[k], pl.p_count[k]);
+    gemm(std::integral_constant<int, 1>(), pl.e_first[k], pl.e_count[k]);
     if (ev) (void)hipEventRecord(ev[1], st);
   }
 };
