@@ -374,9 +374,14 @@ void apply_stencil(oras_ctx c, const C<R>* x, const double2* b, Y* y, int s, hip
   launch_stencil_mf<R, Y>(mf_view<R>(c), x, b, y, c->nx, c->ny, c->nz, s, st);
 }
 
-int nblk_for(long long n) {
-  long long b = (n + 255) / 256;
-  return (int)std::max(1LL, std::min(2048LL, b));
+// Work-groups of the passes over a block of vectors (256 threads, a thread per
+// node and column and iteration): up to 2048, which fills the chip several
+// times; fewer only where there is less than an iteration for each.  (One per
+// 256 nodes left 32^3 nodes with 8 columns 128 work-groups of eight iterations:
+// with a mean of 7 basis vectors the product and update passes took 29.8 and
+// 27.8 us, now 12.8 and 8.0; 61 x 47 x 53 nodes 59.5 and 58.2, now 53.3 and 41.9.)
+int nblk_for(long long n, long long s) {
+  return (int)std::max(1LL, std::min(2048LL, (n * s + 255) / 256));
 }
 
 // y (internal [n][s] c128) = A x in precision prec; x internal c128.
@@ -1452,7 +1457,7 @@ oras_status oras_solve(oras_ctx c, const void* b_dev, void* x_dev, int nrhs, dou
   const size_t zsz = z64 ? sizeof(float2) : sizeof(double2);
   // A z_j in another precision than Z is stored in goes through a converted copy
   const bool convert = (kprec == ORAS_C64) != z64;
-  const int nblk = nblk_for(n);
+  const int nblk = nblk_for(n, s);
   {
     double need = 0;
     if (!c->V.p || c->ws_s < s || c->ws_m < m) need += (double)ns * ((m + 1) * 16.0 + m * zsz + 2 * 16.0);
