@@ -28,8 +28,8 @@
 // A_JI = -A_IJ^T otherwise.  So only the tiles with I <= J are kept up to date,
 // which halves the trailing update that carries almost all the work, and the
 // last pivot block writes the mirror tiles (with every tile updated, 96^3 in 64
-// subdomains took 180 ms a factorisation in complex128, now 101; 160^3 in 512
-// took 224 ms in complex64, now 150).
+// subdomains took 180 ms a factorisation in complex128, now 99; 160^3 in 512
+// took 224 ms in complex64, now 126).
 #include <type_traits>
 #include <utility>
 
@@ -88,26 +88,33 @@ __global__ void __launch_bounds__(256) schur_T_kernel(const SubDesc* subs, int k
     ucol[d][i % TILE] = u;
   }
   __syncthreads();
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    const int c4 = e >> 7, r = (e >> 2) & 31, cl = e & 3;
-    const int a = I * TILE + r, c = J * TILE + c4 * 4 + cl;
-    T acc = czero<T>();
-    if (c < sd.p) {
-      const int cx = c % sd.sx, cy = c / sd.sx;
-      for (int dy = -1; dy <= 1; ++dy) {
-        const int py = cy - dy;
-        if (py < 0 || py >= sd.sy) continue;
-        for (int dx = -1; dx <= 1; ++dx) {
-          const int px = cx - dx;
-          if (px < 0 || px >= sd.sx) continue;
-          const T s = Sinv[mat_off(a, py * sd.sx + px, nt)];
-          cfma(acc, s, ucol[(dy + 1) * 3 + dx + 1][c4 * 4 + cl]);
-        }
-      }
+  // four consecutive columns per thread: per dy they need six consecutive
+  // entries of the row, half the loads of one column per thread, which the
+  // kernel was bound by (512 subdomains of 576-row planes in FP32 927 -> 516 us
+  // a plane, 64 of 800 in FP64 292 -> 245; S_k below 827 -> 500 in FP32).
+  // Indices are clamped to the plane: a neighbour outside the box has a zero
+  // coupling.
+  const int c4 = threadIdx.x >> 5, r = threadIdx.x & 31;
+  const T* row = Sinv + tile_off(I, 0, nt) + r * 4;
+  T acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = czero<T>();
+#pragma unroll
+  for (int dy = -1; dy <= 1; ++dy) {
+    T v[6];
+#pragma unroll
+    for (int o = 0; o < 6; ++o) {
+      const int c = min(max(J * TILE + c4 * 4 - dy * sd.sx + o - 1, 0), sd.P - 1);
+      v[o] = row[(c >> 2) * (4 * TILE) + (c & 3)];
     }
-    Tm[tile_off(I, J, nt) + e] = acc;
+#pragma unroll
+    for (int dx = -1; dx <= 1; ++dx)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) cfma(acc[j], v[j + 1 - dx], ucol[(dy + 1) * 3 + dx + 1][c4 * 4 + j]);
   }
+  T* out = Tm + tile_off(I, J, nt) + c4 * (4 * TILE) + r * 4;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) out[j] = acc[j];
 }
 
 // S_k = D_k - L_k T  (just D_k on the first plane), identity on the pad: the
@@ -145,34 +152,48 @@ __global__ void __launch_bounds__(256) build_S_kernel(const SubDesc* subs, int k
     }
     __syncthreads();
   }
-  for (int q = 0; q < 4; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    const int c4 = e >> 7, r = (e >> 2) & 31, cl = e & 3;
-    const int b = I * TILE + r, c = J * TILE + c4 * 4 + cl;
-    T v = czero<T>();
-    if (b >= sd.p || c >= sd.p) {
-      if (b == c) v = cone<T>();
-    } else {
+  // NC consecutive columns per thread: four in FP32 (one run of the tile layout
+  // per neighbouring row of T), one in FP64, whose 64-byte run would leave a
+  // lane's loads that far apart.  Rows outside the box are clamped, their
+  // coupling is zero.
+  constexpr int NC = sizeof(R) == 4 ? 4 : 1;
+#pragma unroll
+  for (int q = 0; q < 4 / NC; ++q) {
+    const int e = (threadIdx.x + 256 * q) * NC;
+    const int b = I * TILE + ((e >> 2) & 31), c0 = J * TILE + (e >> 7) * 4 + (e & 3);
+    T v[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) v[j] = czero<T>();
+    if (b < sd.p) {
       const int bx = b % sd.sx, by = b / sd.sx;
-      const int cx = c % sd.sx, cy = c / sd.sx;
       const long long node = ((long long)k * sd.sy + by) * sd.sx + bx;
-      const int dx = cx - bx, dy = cy - by;
-      if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1) v = L[eidx(dx, dy, 0) * nbox + node];
-      if (k > 0) {
-        for (int ey = -1; ey <= 1; ++ey) {
-          const int qy = by + ey;
-          if (qy < 0 || qy >= sd.sy) continue;
-          for (int ex = -1; ex <= 1; ++ex) {
-            const int qx = bx + ex;
-            if (qx < 0 || qx >= sd.sx) continue;
-            const T t = Tm[mat_off(qy * sd.sx + qx, c, nt)];
-            cfms(v, lrow[(ey + 1) * 3 + ex + 1][r], t);
-          }
-        }
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        const int c = c0 + j, dx = c % sd.sx - bx, dy = c / sd.sx - by;
+        if (c < sd.p && dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1)
+          v[j] = L[eidx(dx, dy, 0) * nbox + node];
       }
-      big = fmax(big, (double)v.x * v.x + (double)v.y * v.y);
+      if (k > 0) {
+#pragma unroll
+        for (int ey = -1; ey <= 1; ++ey)
+#pragma unroll
+          for (int ex = -1; ex <= 1; ++ex) {
+            const int n = min(max(by + ey, 0), sd.sy - 1) * sd.sx + min(max(bx + ex, 0), sd.sx - 1);
+            const T* t = Tm + mat_off(n, c0, nt);
+            const T l = lrow[(ey + 1) * 3 + ex + 1][(e >> 2) & 31];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) cfms(v[j], l, t[j]);
+          }
+      }
     }
-    S[tile_off(I, J, nt) + e] = v;
+    T* out = S + tile_off(I, J, nt) + e;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int c = c0 + j;
+      if (b < sd.p && c < sd.p) big = fmax(big, (double)v[j].x * v[j].x + (double)v[j].y * v[j].y);
+      else v[j] = b == c ? cone<T>() : czero<T>();
+      out[j] = v[j];
+    }
   }
   red[threadIdx.x] = big;
   __syncthreads();
@@ -403,8 +424,13 @@ __device__ inline int lds_tile(int r, int c) { return (c >> 2) * (TILE * 4 + 4) 
 __device__ inline int lds_entry(int e) { return e + (e >> 7) * 4; }
 
 // One wave's 32 x 32 complex tile product on MFMA: acc += X Y with X a 32 x 32
-// tile in memory (tile layout) and Y one in LDS.  visit(row, col, value)
-// walks the lane's 16 entries of the result.
+// tile in memory (tile layout, fetched into registers) and Y one in LDS in the
+// form OPERAND (OPERAND_BYTES), written from memory by the four waves of a
+// work-group together (fetch_y, stage_y) or from registers (put).
+// The instruction forms Y^T X^T, whose lanes hold a row of the result in runs of
+// consecutive columns: whole lines of the tile layout per load and store (with
+// X Y a lane held a column, 32-byte pieces of sixteen lines per instruction).
+// visit(row, col, value) walks the lane's 16 entries of the result.
 template <typename R> struct TileMma;
 
 // Complex FP32 on the bf16 instruction (32x32x16) with exactly split operands
@@ -414,9 +440,13 @@ template <typename R> struct TileMma;
 // a lane (r = l % 32, g = l / 32) holds X entries (r, 4 q + 2 g + e) of the
 // tile layout (four float4 loads, q = 0..3, e = 0..1) and the Y entries
 // (4 q + 2 g + e, r) of column r, so value i = 2 q + e of both operands refers
-// to the same k.
+// to the same k.  Y is kept split: per half tile six blocks (pieces 1 - 3 of the
+// real part, of the imaginary part) of one 16-byte group per lane.
 template <> struct TileMma<float> {
+  static constexpr int OPERAND_BYTES = 12 * 64 * 16;
   f32x16 accR, accI;
+  float4 x[8];
+  float2 y[4];
   __device__ void zero() {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
@@ -424,27 +454,48 @@ template <> struct TileMma<float> {
       accI[j] = 0.f;
     }
   }
-  __device__ void mac(const float2* __restrict__ X, const float2* __restrict__ Y) {
-    const int lane = threadIdx.x & 63, rr = lane & 31, g = lane >> 5;
-    const float4* X4 = reinterpret_cast<const float4*>(X);
+  __device__ void fetch_x(const float2* __restrict__ X, int q0 = 0, int q1 = 8) {
+    const int lane = threadIdx.x & 63;
+    const float4* X4 = reinterpret_cast<const float4*>(X) + (lane & 31) * 2 + (lane >> 5);
+#pragma unroll
+    for (int q = q0; q < q1; ++q) x[q] = X4[q * 64];
+  }
+  // wave w: half tile w % 2, values 4 (w / 2) .. + 3 of each lane
+  __device__ void fetch_y(const float2* __restrict__ Y) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      y[j] = Y[in_tile(16 * (w & 1) + 8 * (w >> 1) + 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1),
+                       lane & 31)];
+  }
+  __device__ void stage_y(void* lds) const { put(lds, threadIdx.x >> 6, y); }
+  static __device__ void put(void* lds, int w, const float2 (&v)[4]) {
+    unsigned pr[3][2], pi[3][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      split3(v[2 * h].x, v[2 * h + 1].x, pr[0][h], pr[1][h], pr[2][h]);
+      split3(v[2 * h].y, v[2 * h + 1].y, pi[0][h], pi[1][h], pi[2][h]);
+    }
+    uint2* o = reinterpret_cast<uint2*>(lds) + ((w & 1) * 6 * 64 + (threadIdx.x & 63)) * 2 + (w >> 1);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      o[q * 128] = make_uint2(pr[q][0], pr[q][1]);
+      o[(3 + q) * 128] = make_uint2(pi[q][0], pi[q][1]);
+    }
+  }
+  // next: the X tile to fetch as the registers of this one come free
+  __device__ void mac(const void* lds, const float2* __restrict__ next) {
+    const u32x4* Y = reinterpret_cast<const u32x4*>(lds) + (threadIdx.x & 63);
     const u32x4 sgn = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
 #pragma unroll
     for (int hj = 0; hj < 2; ++hj) {
-      float4 a[4];
-      float2 y[8];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a[q] = X4[(4 * hj + q) * 64 + rr * 2 + g];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) y[i] = Y[lds_tile(16 * hj + 4 * (i >> 1) + 2 * g + (i & 1), rr)];
       unsigned r1[4], r2[4], r3[4], i1[4], i2[4], i3[4];
-      unsigned s1[4], s2[4], s3[4], t1[4], t2[4], t3[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        split3(a[q].x, a[q].z, r1[q], r2[q], r3[q]);
-        split3(a[q].y, a[q].w, i1[q], i2[q], i3[q]);
-        split3(y[2 * q].x, y[2 * q + 1].x, s1[q], s2[q], s3[q]);
-        split3(y[2 * q].y, y[2 * q + 1].y, t1[q], t2[q], t3[q]);
+        split3(x[4 * hj + q].x, x[4 * hj + q].z, r1[q], r2[q], r3[q]);
+        split3(x[4 * hj + q].y, x[4 * hj + q].w, i1[q], i2[q], i3[q]);
       }
+      fetch_x(next, 4 * hj, 4 * hj + 4);
       const bf16x8 Xr1 = as_bf16x8(u32x4{r1[0], r1[1], r1[2], r1[3]});
       const bf16x8 Xr2 = as_bf16x8(u32x4{r2[0], r2[1], r2[2], r2[3]});
       const bf16x8 Xr3 = as_bf16x8(u32x4{r3[0], r3[1], r3[2], r3[3]});
@@ -454,17 +505,14 @@ template <> struct TileMma<float> {
       const bf16x8 Xn1 = as_bf16x8(u32x4{i1[0], i1[1], i1[2], i1[3]} ^ sgn);
       const bf16x8 Xn2 = as_bf16x8(u32x4{i2[0], i2[1], i2[2], i2[3]} ^ sgn);
       const bf16x8 Xn3 = as_bf16x8(u32x4{i3[0], i3[1], i3[2], i3[3]} ^ sgn);
-      const bf16x8 Yr1 = as_bf16x8(u32x4{s1[0], s1[1], s1[2], s1[3]});
-      const bf16x8 Yr2 = as_bf16x8(u32x4{s2[0], s2[1], s2[2], s2[3]});
-      const bf16x8 Yr3 = as_bf16x8(u32x4{s3[0], s3[1], s3[2], s3[3]});
-      const bf16x8 Yi1 = as_bf16x8(u32x4{t1[0], t1[1], t1[2], t1[3]});
-      const bf16x8 Yi2 = as_bf16x8(u32x4{t2[0], t2[1], t2[2], t2[3]});
-      const bf16x8 Yi3 = as_bf16x8(u32x4{t3[0], t3[1], t3[2], t3[3]});
+      const bf16x8 Yr1 = as_bf16x8(Y[(6 * hj + 0) * 64]), Yr2 = as_bf16x8(Y[(6 * hj + 1) * 64]);
+      const bf16x8 Yr3 = as_bf16x8(Y[(6 * hj + 2) * 64]), Yi1 = as_bf16x8(Y[(6 * hj + 3) * 64]);
+      const bf16x8 Yi2 = as_bf16x8(Y[(6 * hj + 4) * 64]), Yi3 = as_bf16x8(Y[(6 * hj + 5) * 64]);
 #define ORAS_X3(XR, XI, XN, YR, YI)                                              \
-  accR = __builtin_amdgcn_mfma_f32_32x32x16_bf16(XR, YR, accR, 0, 0, 0);         \
-  accI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(XR, YI, accI, 0, 0, 0);         \
-  accR = __builtin_amdgcn_mfma_f32_32x32x16_bf16(XN, YI, accR, 0, 0, 0);         \
-  accI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(XI, YR, accI, 0, 0, 0);
+  accR = __builtin_amdgcn_mfma_f32_32x32x16_bf16(YR, XR, accR, 0, 0, 0);         \
+  accI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(YI, XR, accI, 0, 0, 0);         \
+  accR = __builtin_amdgcn_mfma_f32_32x32x16_bf16(YI, XN, accR, 0, 0, 0);         \
+  accI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(YR, XI, accI, 0, 0, 0);
       ORAS_X3(Xr1, Xi1, Xn1, Yr1, Yi1)
       ORAS_X3(Xr1, Xi1, Xn1, Yr2, Yi2)
       ORAS_X3(Xr2, Xi2, Xn2, Yr1, Yi1)
@@ -474,46 +522,59 @@ template <> struct TileMma<float> {
 #undef ORAS_X3
     }
   }
-  // accumulator item i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
+  // accumulator item i of lane l: row l % 32, column 8 (i / 4) + 4 (l / 32) + i % 4
   template <typename F> __device__ void visit(F f) const {
     const int lane = threadIdx.x & 63, rr = lane & 31, g = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = 8 * (i / 4) + 4 * g + (i % 4);
-      f(row, rr, make_float2(accR[i], accI[i]));
-    }
+    for (int i = 0; i < 16; ++i) f(rr, 8 * (i / 4) + 4 * g + (i % 4), make_float2(accR[i], accI[i]));
   }
 };
 
 // Complex FP64 on the 16x16x4 FP64 instruction: two 16-row halves x two
 // 16-column halves, the real and imaginary parts of the result in separate
-// accumulators.
+// accumulators.  Y is kept as the tile with padded column groups (lds_tile).
 template <> struct TileMma<double> {
+  static constexpr int OPERAND_BYTES = LTILE * (int)sizeof(double2);
   f64x4 acc[2][2][2];
+  double2 x[16], y[4];
   __device__ void zero() {
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i >> 2][(i >> 1) & 1][i & 1] = f64x4{0, 0, 0, 0};
   }
-  __device__ void mac(const double2* __restrict__ X, const double2* __restrict__ Y) {
+  __device__ void fetch_x(const double2* __restrict__ X, int i0 = 0, int i1 = 16) {
     const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
-#pragma unroll 4
-    for (int q = 0; q < 8; ++q) {
-      double2 x[2], y[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        x[h] = X[(q * TILE + 16 * h + m) * 4 + kk];
-        y[h] = Y[lds_tile(4 * q + kk, 16 * h + m)];
-      }
+    for (int i = i0; i < i1; ++i) x[i] = X[((i >> 1) * TILE + 16 * (i & 1) + m) * 4 + kk];
+  }
+  __device__ void fetch_y(const double2* __restrict__ Y) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = Y[threadIdx.x + 256 * j];
+  }
+  __device__ void stage_y(void* lds) const {
+    double2* o = reinterpret_cast<double2*>(lds);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[lds_entry(threadIdx.x + 256 * j)] = y[j];
+  }
+  __device__ void mac(const void* lds, const double2* __restrict__ next) {
+    const double2* Y = reinterpret_cast<const double2*>(lds);
+    const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      double2 v[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) v[h] = Y[lds_tile(4 * q + kk, 16 * h + m)];
 #pragma unroll
       for (int rs = 0; rs < 2; ++rs)
 #pragma unroll
         for (int ns = 0; ns < 2; ++ns) {
+          const double2 u = x[2 * q + rs];
           f64x4 &re = acc[rs][ns][0], &im = acc[rs][ns][1];
-          re = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].x, y[ns].x, re, 0, 0, 0);
-          im = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].x, y[ns].y, im, 0, 0, 0);
-          re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[rs].y, y[ns].y, re, 0, 0, 0);
-          im = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rs].y, y[ns].x, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].x, u.x, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].y, u.x, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].y, -u.y, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].x, u.y, im, 0, 0, 0);
         }
+      fetch_x(next, 2 * q, 2 * q + 2);
     }
   }
   template <typename F> __device__ void visit(F f) const {
@@ -524,24 +585,26 @@ template <> struct TileMma<double> {
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int ns = 0; ns < 2; ++ns)
-          f(rs * 16 + kk + 4 * t, 16 * ns + m,
+          f(rs * 16 + m, 16 * ns + kk + 4 * t,
             make_double2(acc[rs][ns][0][t], acc[rs][ns][1][t]));
   }
 };
 
 // The panels of one pivot block, for one tile index J outside it (one
 // work-group of NBT waves per (J, subdomain)): wave t writes
-//   C_J,t  the old A_Jk (tile t of the row, the update's left operand),
-//   W_J,t  the new A_kJ = A_kk^{-1} A_kJ (the update's right operand)
-// to the plane's scratch (C tiles of all J, then W tiles), and W_J,t to its
-// place, which for J before the pivot block is the transposed tile (J, kb0 + t).
+//   C_J,t  the old A_Jk (tile t of the row, the update's left operand) to the
+//          plane's scratch (C tiles of all J, then W tiles),
+//   W_J,t  the new A_kJ = A_kk^{-1} A_kJ (the update's right operand) to its
+//          place for J after the pivot block; for J before it, whose place
+//          holds the transposed tile (J, kb0 + t), to both.
 // The last pivot block of a plane also writes the tile's mirror.
 template <typename R>
 __global__ void __launch_bounds__(64 * GjBlock<R>::NBT)
 gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   using T = C<R>;
+  using M = TileMma<R>;
   constexpr int NBT = GjBlock<R>::NBT, TT = TILE * TILE;
-  __shared__ __align__(16) T sY[NBT][LTILE];
+  __shared__ __align__(16) unsigned char lds[NBT][M::OPERAND_BYTES];
   const SubDesc sd = subs[blockIdx.y];
   const int J = blockIdx.x;
   if (k >= sd.sz || kb0 >= sd.nt || J >= sd.nt) return;
@@ -552,8 +615,10 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   T* Cs = tbuf + sd.t_off + (long long)J * NBT * TT;
   T* Ws = Cs + (long long)sd.nt * NBT * TT;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  M mm;
   if (wv < nb) {
     const T* g = base + (after ? tile_off(kb0 + wv, J, sd.nt) : tile_off(J, kb0 + wv, sd.nt));
+    T* sY = reinterpret_cast<T*>(lds[wv]);
 #pragma unroll 4
     for (int i = 0; i < TT / 64; ++i) {
       // entry e of the tile: row r, column c
@@ -564,71 +629,110 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
         v.x = -v.x;
         v.y = -v.y;
       }
-      sY[wv][after ? lds_tile(r, c) : lds_tile(c, r)] = v;
+      sY[after ? lds_tile(r, c) : lds_tile(c, r)] = v;
+    }
+    if constexpr (sizeof(R) == 4) {
+      // the wave's own tile: columns into registers, then split in its place
+      float2 v[4][4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          v[w][j] = sY[lds_tile(16 * (w & 1) + 8 * (w >> 1) + 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1),
+                                lane & 31)];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int w = 0; w < 4; ++w) M::put(sY, w, v[w]);
     }
   }
   __syncthreads();
   if (wv >= nb) return;
-  TileMma<R> mm;
   mm.zero();
-  for (int u = 0; u < nb; ++u) mm.mac(base + tile_off(kb0 + wv, kb0 + u, sd.nt), sY[u]);
-  T* up = base + (after ? tile_off(kb0 + wv, J, sd.nt) : tile_off(J, kb0 + wv, sd.nt));
-  T* lo = base + tile_off(kb0 + wv, J, sd.nt);     // the mirror (J before the pivot block)
+  const T* D = base + tile_off(kb0 + wv, kb0, sd.nt);
+  mm.fetch_x(D);
+  for (int u = 0; u < nb; ++u) {
+    mm.mac(lds[u], D + min(u + 1, nb - 1) * TT);
+    asm volatile("" ::: "memory");      // keeps the fetch in this iteration
+  }
+  T* lo = base + tile_off(kb0 + wv, J, sd.nt);     // its place, or the mirror of it
+  T* up = base + tile_off(J, kb0 + wv, sd.nt);
   mm.visit([&](int row, int col, T v) {
-    Ws[wv * TT + in_tile(row, col)] = v;
-    up[after ? in_tile(row, col) : in_tile(col, row)] = v;
-    if (last && !after) lo[in_tile(row, col)] = v;
+    if (!after) {
+      Ws[wv * TT + in_tile(row, col)] = v;
+      up[in_tile(col, row)] = v;
+    }
+    if (after || last) lo[in_tile(row, col)] = v;
   });
 }
 
 // A_IJ <- A_IJ - C_I W_J (I <= J, both outside the pivot block): one wave per
-// tile.  For each pivot tile u the tile W_J,u is staged in LDS and C_I,u is
-// read from memory directly as the row operand; the tile A_IJ is read after
-// the products.  One LDS tile and few live registers let several waves share
-// a SIMD.  Work-group ids are mapped so that all tiles of one subdomain run on
-// the same XCD and read the panels from its L2.  The last pivot block of a
-// plane also writes the mirror tile.
+// tile, four row tiles I of a column J per work-group.  Per pivot tile u the
+// four waves stage W_J,u in LDS together (two buffers, one barrier per u; in
+// FP32 already split for the products) and each reads its C_I,u from memory;
+// both of the next u are fetched while the current one feeds the products.
+// Work-group ids are mapped so that all tiles of one subdomain run on the same
+// XCD and read the panels from its L2.  The last pivot block of a plane also
+// writes the mirror tile.
+// On 512 subdomains of 576-row planes in FP32 a call takes 398 us (429 with one
+// wave per work-group that staged and split W for itself), of which the tiles'
+// own traffic is 170 and the matrix unit 134; on 64 of 800-row planes in FP64
+// 171, of which either is about 100.  Four columns per work-group, to amortise
+// its start, changed nothing in FP32 and spilled in FP64 (206).
 constexpr int NXCD = 8;
+constexpr int UW = 4;      // waves, row tiles, of an update work-group
+// Work-groups of nt tile columns: column J has J / UW + 1 groups of row tiles,
+// column a UW + b starts at (a + 1) (a UW / 2 + b).
+__host__ __device__ inline int update_items(int nt) {
+  const int a = nt / UW, b = nt % UW;
+  return (a + 1) * (a * UW / 2 + b);
+}
 template <typename R>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(64 * UW) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 3 : 2)))
 gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>* fac,
                  const C<R>* tbuf) {
   using T = C<R>;
+  using M = TileMma<R>;
   constexpr int NBT = GjBlock<R>::NBT, TT = TILE * TILE;
-  __shared__ __align__(16) T sY[LTILE];
-  const int bid = blockIdx.x, r = bid / NXCD, items = max_nt * (max_nt + 1) / 2;
+  __shared__ __align__(16) unsigned char lds[2][M::OPERAND_BYTES];
+  const int bid = blockIdx.x, r = bid / NXCD, items = update_items(max_nt);
   const int sub = (r / items) * NXCD + bid % NXCD, item = r % items;
   if (sub >= nsub) return;
   const SubDesc sd = subs[sub];
-  // item = J (J + 1) / 2 + I
-  int J = (int)((sqrtf(8.f * item + 1.f) - 1.f) * 0.5f);
-  J += (J + 1) * (J + 2) / 2 <= item;
-  J -= J * (J + 1) / 2 > item;
-  const int I = item - J * (J + 1) / 2;
+  // item -> column J = UW a + b and row group g
+  int a = (int)((sqrtf(1.f + 8.f * item / UW) - 1.f) * 0.5f);
+  a += update_items((a + 1) * UW) <= item;
+  a -= update_items(a * UW) > item;
+  const int rest = item - update_items(a * UW), J = UW * a + rest / (a + 1), g = rest % (a + 1);
   if (k >= sd.sz || kb0 >= sd.nt || J >= sd.nt) return;
   const int nb = min(NBT, sd.nt - kb0);
-  if ((I >= kb0 && I < kb0 + nb) || (J >= kb0 && J < kb0 + nb)) return;
-  const bool last = kb0 + nb == sd.nt;
+  if (J >= kb0 && J < kb0 + nb) return;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), I = UW * g + wv;
+  const bool live = I <= J && !(I >= kb0 && I < kb0 + nb), last = kb0 + nb == sd.nt;
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
   T* Aij = base + tile_off(I, J, sd.nt);
   T* Aji = base + tile_off(J, I, sd.nt);
   const T* Cs = tbuf + sd.t_off + (long long)I * NBT * TT;
-  const T* Ws = tbuf + sd.t_off + (long long)(sd.nt + J) * NBT * TT;
-  const int lane = threadIdx.x & 63;
-  TileMma<R> mm;
+  // W_J: in its place after the pivot block, in the scratch before it
+  const T* Ws = J > kb0 ? base + tile_off(kb0, J, sd.nt)
+                        : tbuf + sd.t_off + (long long)(sd.nt + J) * NBT * TT;
+  const long long wstep = J > kb0 ? (long long)sd.nt * TT : TT;
+  M mm;
   mm.zero();
+  mm.fetch_y(Ws);
+  if (live) mm.fetch_x(Cs);
   for (int u = 0; u < nb; ++u) {
-#pragma unroll 4
-    for (int i = 0; i < TT / 64; ++i) sY[lds_entry(i * 64 + lane)] = Ws[u * TT + i * 64 + lane];
+    mm.stage_y(lds[u & 1]);
     __syncthreads();
-    mm.mac(Cs + u * TT, sY);
-    __syncthreads();
+    mm.fetch_y(Ws + min(u + 1, nb - 1) * wstep);
+    if (live) mm.mac(lds[u & 1], Cs + min(u + 1, nb - 1) * TT);
+    asm volatile("" ::: "memory");      // keeps the fetches in this iteration
   }
   T cv[16];
-  {
+  if (live) {
     int n = 0;
     mm.visit([&](int row, int col, T) { cv[n++] = Aij[in_tile(row, col)]; });
   }
+  if (!live) return;
   int n = 0;
   mm.visit([&](int row, int col, T v) {
     const T w = csub(cv[n], v);
@@ -662,7 +766,7 @@ void launch_factor_plane(const SubDesc* subs_dev, int nsub, int k, int max_nt, i
     hipLaunchKernelGGL((gj_panel_kernel<R>), dim3(max_nt, nsub), dim3(64 * NBT), 0, st,
                        subs_dev, k, kb0, fac, tbuf);
     hipLaunchKernelGGL((gj_update_kernel<R>),
-                       dim3((unsigned)(nsub8 * (max_nt * (max_nt + 1) / 2))), dim3(64), 0, st,
+                       dim3((unsigned)(nsub8 * update_items(max_nt))), dim3(64 * UW), 0, st,
                        subs_dev, nsub, max_nt, k, kb0, fac, tbuf);
   }
 }
