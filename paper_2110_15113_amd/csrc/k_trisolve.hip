@@ -462,8 +462,11 @@ template <int NT> __device__ inline double2 buf_ld(BufRsrc r, int vo, int so) {
 }
 
 // Y_k (=|-=) S_k^{-1} t for 16 RS rows and one column group per work-group of
-// KS waves, each taking a KS-th of the k range; the waves' sums meet in LDS in
-// a fixed order.  Each wave keeps PF k-steps of both operands in flight.
+// KS waves, each taking a KS-th of the k range; the waves' sums meet in LDS and
+// each wave adds up and stores its share, in a fixed order (a plane step on a
+// 32^3 grid with one right-hand side 10.4 us; 11 where halves of the waves hand
+// their sums on and one wave stores).  Each wave keeps PF k-steps of both
+// operands in flight.
 //
 // A column group is NC blocks of 16 columns with the real and imaginary parts
 // of the result in separate accumulators (Re += Ar Br - Ai Bi, Im += Ar Bi +
@@ -486,10 +489,13 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
                       int bwd, const double2* __restrict__ fac, const double2* __restrict__ tvbuf,
                       double2* __restrict__ ybuf, double2* __restrict__ z, int nx, int ny, int s,
                       int c0base) {
-  constexpr int HW = KS > 1 ? KS / 2 : 1;
   constexpr int NB = NC ? NC : 1;          // t blocks loaded per k-step
   constexpr int NA = NC ? 2 * NC : 1;      // accumulators per 16 rows
-  __shared__ double red[HW][RS * NA * 4][64];
+  // results per lane (complex values, or single parts for NC = 0), and how many
+  // of them a wave adds up and stores (waves from NE / EW on: none)
+  using OT = typename std::conditional<(NC > 0), double2, double>::type;
+  constexpr int NE = RS * NB * 4, EW = NE > KS ? NE / KS : 1;
+  __shared__ OT red[KS][NE][64];
   int sub, item;
   xcd_map(max_rg * ncg, sub, item);
   if (sub >= nsub) return;
@@ -564,70 +570,54 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
       }
     }
   }
-  // the upper half of the waves hands its sums to the lower half until one is left
+  // result item e of a lane: 16-row half e / (4 NB), column block (e / 4) % NB,
+  // i = e % 4: row kk + 4 i of the half, instruction column m
 #pragma unroll
-  for (int h = KS / 2; h > 0; h >>= 1) {
-    if (wv >= h && wv < 2 * h) {
-#pragma unroll
-      for (int rs = 0; rs < RS; ++rs)
-#pragma unroll
-        for (int na = 0; na < NA; ++na)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) red[wv - h][(rs * NA + na) * 4 + i][lane] = acc[rs][na][i];
-    }
-    __syncthreads();
-    if (wv < h) {
-#pragma unroll
-      for (int rs = 0; rs < RS; ++rs)
-#pragma unroll
-        for (int na = 0; na < NA; ++na)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[rs][na][i] += red[wv][(rs * NA + na) * 4 + i][lane];
-    }
-    if (h > 1) __syncthreads();
+  for (int e = 0; e < NE; ++e) {
+    const int rs = e / (4 * NB), nb = (e >> 2) % NB, i = e & 3;
+    if constexpr (NC > 0) red[wv][e][lane] = make_double2(acc[rs][2 * nb][i], acc[rs][2 * nb + 1][i]);
+    else red[wv][e][lane] = acc[rs][0][i];
   }
-  if (wv > 0) return;
-  // result item i of a lane: row kk + 4 i, instruction column m
-  using OT = typename std::conditional<(NC > 0), double2, double>::type;
   OT* Yk = reinterpret_cast<OT*>(ybuf + (sd.y_off + (long long)k * P) * s + c0) + m;
   const int rstride = NC ? s : 2 * s;
   const bool final_plane = bwd || (k == sd.sz - 1);
+  if (wv * EW >= NE) {
+    __syncthreads();
+    return;
+  }
+  // the old values first: their loads are in flight while the waves meet
+  OT old[EW];
 #pragma unroll
-  for (int rs = 0; rs < RS; ++rs) {
-    OT old[4][NB];
+  for (int j = 0; j < EW; ++j) {
+    const int e = wv * EW + j, nb = (e >> 2) % NB;
+    old[j] = OT{};
+    if (bwd)
+      old[j] = Yk[(long long)(row0 + 16 * (e / (4 * NB)) + kk + 4 * (e & 3)) * rstride +
+                  (NC && c0 + 16 * nb + m >= s ? 0 : 16 * nb)];
+  }
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < EW; ++j) {
+    const int e = wv * EW + j, nb = (e >> 2) % NB;
+    const int row = row0 + 16 * (e / (4 * NB)) + kk + 4 * (e & 3);
+    if (NC && c0 + 16 * nb + m >= s) continue;
+    OT val = red[0][e][lane];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if (bwd) old[i][nb] = Yk[(long long)(row0 + rs * 16 + kk + 4 * i) * rstride +
-                                 (NC && c0 + 16 * nb + m >= s ? 0 : 16 * nb)];
-        else old[i][nb] = OT{};
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = row0 + rs * 16 + kk + 4 * i;
-      long long zoff = -1;
-      if (final_plane && row < sd.p) {
-        const int qx = row % sd.sx, qy = row / sd.sx;
-        const int gx = sd.lo[0] + qx, gy = sd.lo[1] + qy, gz = sd.lo[2] + k;
-        if (gx >= sd.olo[0] && gx < sd.ohi[0] && gy >= sd.olo[1] && gy < sd.ohi[1] &&
-            gz >= sd.olo[2] && gz < sd.ohi[2])
-          zoff = (((long long)gz * ny + gy) * nx + gx) * s + c0;
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if (NC && c0 + 16 * nb + m >= s) continue;
-        OT val;
-        if constexpr (NC > 0) {
-          val = make_double2(acc[rs][2 * nb][i], acc[rs][2 * nb + 1][i]);
-          if (bwd) val = make_double2(old[i][nb].x - val.x, old[i][nb].y - val.y);
-        } else {
-          val = acc[rs][0][i];
-          if (bwd) val = old[i][nb] - val;
-        }
-        Yk[(long long)row * rstride + 16 * nb] = val;
-        if (zoff >= 0) reinterpret_cast<OT*>(z + zoff)[16 * nb + m] = val;
-      }
+    for (int w = 1; w < KS; ++w) {
+      if constexpr (NC > 0) val = cadd(val, red[w][e][lane]);
+      else val += red[w][e][lane];
+    }
+    if (bwd) {
+      if constexpr (NC > 0) val = csub(old[j], val);
+      else val = old[j] - val;
+    }
+    Yk[(long long)row * rstride + 16 * nb] = val;
+    if (final_plane && row < sd.p) {
+      const int qx = row % sd.sx, qy = row / sd.sx;
+      const int gx = sd.lo[0] + qx, gy = sd.lo[1] + qy, gz = sd.lo[2] + k;
+      if (gx >= sd.olo[0] && gx < sd.ohi[0] && gy >= sd.olo[1] && gy < sd.ohi[1] &&
+          gz >= sd.olo[2] && gz < sd.ohi[2])
+        reinterpret_cast<OT*>(z + (((long long)gz * ny + gy) * nx + gx) * s + c0)[16 * nb + m] = val;
     }
   }
 }
