@@ -81,7 +81,7 @@ def test_matrix_free_apply_after_set_m():
 
 
 # grids whose applies run tiles of 2, 4, 8 and 16 planes (8 x 8 columns, the
-# tallest with 512 work items): 25 x 2, 25 x 11 x 2, 36 x 5 x 3 and 64 x 3 x 3
+# tallest with 400 work items): 25 x 2, 25 x 11 x 2, 36 x 5 x 3 and 64 x 3 x 3
 # tiles times chunks of 16
 @pytest.mark.parametrize("n,nrhs", [((33, 34, 3), 1), ((33, 34, 41), 17), ((41, 42, 37), 33),
                                     ((57, 58, 33), 35)])
@@ -102,3 +102,20 @@ def test_apply_of_caller_arrays(n, nrhs):
         if nrhs * w.nx * w.ny * w.nz * 40 < 5e7:
             S.apply_A_noalloc(xd, xd, prec=prec)      # in place
             assert _row_err(xd.cpu().numpy(), ref, scale) < bar
+
+
+# 64 x 3 tiles, some of them PML-free, in 3 and in 4 chunks of 16: below and at
+# the 768 work items from which PML-free tiles have a launch of their own (the
+# 24 columns: one chunk of 16 and one of 8)
+@pytest.mark.parametrize("nrhs", [24, 48, 64])
+def test_apply_in_one_launch_or_two(nrhs):
+    need_gpu()
+    w = wl.small_random((57, 58, 33), npml=4, q=70.0, seed=63)
+    S = setup(w, prec=1)
+    x = rand_field((w.nz, w.ny, w.nx), nrhs, 64)
+    C = op.row_coeffs(oracle_fields(w))
+    ref = op.apply_coeffs(C, x)
+    scale = op.apply_coeffs(np.abs(C), np.abs(x)).real
+    for prec, bar in ((2, FP64_ROW), (1, FP32_ROW)):
+        y = S.apply_A(to_dev(x, S), prec=prec)
+        assert _row_err(y.cpu().numpy(), ref, scale) < bar
