@@ -249,6 +249,32 @@ template <int N> __device__ inline double row_bcast(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// the 16 lanes G of a wave, to each 16 lanes of it
+template <int G> __device__ inline unsigned group_bcast(unsigned v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);    // groups 0 0 2 2, 1 1 3 3
+  const unsigned w = a[G & 1];
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);    // the lower, the upper
+  return b[G >> 1];
+}
+template <int G> __device__ inline float group_bcast(float v) {
+  return __uint_as_float(group_bcast<G>(__float_as_uint(v)));
+}
+template <int G> __device__ inline double group_bcast(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned long long lo = group_bcast<G>((unsigned)u), hi = group_bcast<G>((unsigned)(u >> 32));
+  return __longlong_as_double((long long)(hi << 32 | lo));
+}
+// lane L's value, uniform
+template <int L> __device__ inline float lane_value(float v) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
+}
+template <int L> __device__ inline double lane_value(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffLL), L);
+  const int hi = __builtin_amdgcn_readlane((int)(u >> 32), L);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 template <int... I, typename F>
 __device__ inline void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
   (f(std::integral_constant<int, I>()), ...);
@@ -260,9 +286,11 @@ template <int N, typename F> __device__ inline void static_for(F&& f) {
 
 // A <- A^{-1} of a 16 x 16 block at m (row stride ld) by one wave: unblocked
 // Gauss-Jordan in registers, lane (r = l % 16, g = l / 16) holding row r,
-// columns 4 g .. 4 g + 3; the pivot row comes by DPP, the pivot column by a
-// lane exchange, so no pivot step waits at a barrier.  The smallest |pivot|^2
-// of the first `count` pivots goes to mag_min, a zero or non-finite one to bad.
+// columns 4 g .. 4 g + 3; the pivot row comes by DPP, the pivot column by lane
+// swaps, the pivot by a lane read, so no pivot step waits at a barrier or for
+// LDS.  The pivot row itself is 0 - (-1 / p) times the old one, which makes it
+// a row like the others.  The smallest |pivot|^2 of the first `count` pivots
+// goes to mag_min, a zero or non-finite one to bad.
 template <typename R>
 __device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& bad) {
   using T = C<R>;
@@ -272,48 +300,50 @@ __device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& ba
   for (int j = 0; j < 4; ++j) a[j] = m[r * ld + 4 * g + j];
   static_for<16>([&](auto P) {
     constexpr int piv = decltype(P)::value, pg = piv / 4, pj = piv % 4;
+    T p;
+    p.x = lane_value<16 * pg + piv>(a[pj].x);
+    p.y = lane_value<16 * pg + piv>(a[pj].y);
     T rv[4], cv;
-    cv.x = __shfl(a[pj].x, pg * 16 + r, 64);
-    cv.y = __shfl(a[pj].y, pg * 16 + r, 64);
+    cv.x = group_bcast<pg>(a[pj].x);
+    cv.y = group_bcast<pg>(a[pj].y);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       rv[j].x = row_bcast<piv>(a[j].x);
       rv[j].y = row_bcast<piv>(a[j].y);
+      a[j].x = r == piv ? (R)0 : a[j].x;
+      a[j].y = r == piv ? (R)0 : a[j].y;
     }
-    T p;
-    p.x = row_bcast<piv>(cv.x);
-    p.y = row_bcast<piv>(cv.y);
     const R mag = p.x * p.x + p.y * p.y;
-    const bool ok = isfinite(p.x) && isfinite(p.y) && mag > Tiny<R>::v;
-    const R inv = (R)1 / (ok ? mag : (R)1);
-    T ip;
-    ip.x = p.x * inv;
-    ip.y = -p.y * inv;
+    const bool ok = isfinite(p.x) & isfinite(p.y) & (mag > Tiny<R>::v);
     bad |= !ok;
-    if (ok && piv < count) mag_min = fmin(mag_min, mag);
-    const T f = cmul(cv, ip);                        // A_r,piv / p
+    mag_min = ok & (piv < count) & (mag < mag_min) ? mag : mag_min;
+    const R inv = (R)1 / mag;
+    T f;                                             // A_r,piv / p, or -1 / p
+    f.x = (r == piv ? -p.x : cv.x * p.x + cv.y * p.y) * inv;
+    f.y = (r == piv ? p.y : cv.y * p.x - cv.x * p.y) * inv;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      T v = a[j];
-      cfms(v, f, rv[j]);
-      const T w = cmul(rv[j], ip);                   // A_piv,c / p
-      a[j].x = r == piv ? w.x : v.x;
-      a[j].y = r == piv ? w.y : v.y;
-    }
-    if (g == pg) {                                   // -A_r,piv / p
-      a[pj].x = r == piv ? ip.x : -f.x;
-      a[pj].y = r == piv ? ip.y : -f.y;
+    for (int j = 0; j < 4; ++j) cfms(a[j], f, rv[j]);
+    if (g == pg) {                                   // -A_r,piv / p, 1 / p
+      a[pj].x = -f.x;
+      a[pj].y = -f.y;
     }
   });
 #pragma unroll
   for (int j = 0; j < 4; ++j) m[r * ld + 4 * g + j] = a[j];
 }
 
-// One wave's 16 x 16 block: D <- (SUB ? D : 0) -+ X Y (SUB or NEG: minus), all
-// blocks of the LDS matrix with row stride ld.  Every operand is read before
-// D is written, so D may be X or Y.
-template <typename R, bool SUB, bool NEG>
-__device__ inline void block_product(C<R>* D, const C<R>* X, const C<R>* Y, int ld) {
+// One wave's 16 x 16 block: D <- D - X Y (SUB) or X Y, blocks
+// in LDS; YT: minus the transposed block at Y for Y.  Every operand is read
+// before D is written, so D may be any of them.  The result also goes to
+// `mirror` if that is not null, transposed and times sign.
+template <typename R> struct Block {
+  C<R>* p;
+  int ld;        // row stride
+  __device__ C<R>& operator()(int r, int c) const { return p[r * ld + c]; }
+};
+template <typename R, bool SUB, bool YT>
+__device__ inline void block_product(Block<R> D, Block<R> X, Block<R> Y, C<R>* mirror = nullptr,
+                                     R sign = 1) {
   using T = C<R>;
   using M = Mma16<R>;
   const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
@@ -321,14 +351,14 @@ __device__ inline void block_product(C<R>* D, const C<R>* X, const C<R>* Y, int 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     T d = czero<T>();
-    if (SUB) d = D[M::row(kk, i) * ld + m];
+    if (SUB) d = D(M::row(kk, i), m);
     re[i] = d.x;
     im[i] = d.y;
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const T x = X[m * ld + 4 * q + kk], y = Y[(4 * q + kk) * ld + m];
-    const R xr = SUB || NEG ? -x.x : x.x, xi = SUB || NEG ? -x.y : x.y;
+    const T x = X(m, 4 * q + kk), y = YT ? Y(m, 4 * q + kk) : Y(4 * q + kk, m);
+    const R xr = SUB || YT ? -x.x : x.x, xi = SUB || YT ? -x.y : x.y;
     re = M::mac(xr, y.x, re);
     im = M::mac(xr, y.y, im);
     re = M::mac(-xi, y.y, re);
@@ -339,19 +369,30 @@ __device__ inline void block_product(C<R>* D, const C<R>* X, const C<R>* Y, int 
     T d;
     d.x = re[i];
     d.y = im[i];
-    D[M::row(kk, i) * ld + m] = d;
+    D(M::row(kk, i), m) = d;
+    if (mirror) {
+      d.x *= sign;
+      d.y *= sign;
+      mirror[m * D.ld + M::row(kk, i)] = d;
+    }
   }
 }
 
 // A_kk <- A_kk^{-1} for the pivot block (nb tiles from tile kb0), by blocked
 // Gauss-Jordan over 16 x 16 blocks of the matrix in LDS, one work-group per
 // subdomain.  It is a chain (few work-groups, every other kernel of the plane
-// waits for it), so what counts is the length of a step: one wave inverts a
-// 16 x 16 diagonal block in registers while the others finish the previous
-// block column, and the products run on the matrix unit (64 complex FP64 rows
-// 33 us a call where 64 pivot steps with two barriers each took 75; 128 complex
-// FP32 rows on 256 subdomains 131 us against 305; 32^3 in 8 subdomains, which
-// little else but this chain keeps waiting, 12.9 -> 9.0 ms a factorisation).
+// waits for it), so what counts is the length of a step: wave 0 updates and
+// inverts the next diagonal block in registers, ahead of the other waves in
+// instruction priority, while those finish the step, and the products run on
+// the matrix unit.  The matrix stays symmetric but for the sign between
+// eliminated and other blocks, so of A_ij and A_ji one is computed.
+//
+// 64 complex FP64 rows 28 us a call: 64 pivots of 0.27 (about 25 dependent FP64
+// instructions each), the rest are products, loads and stores; 33 with the next
+// inverse after the update and both halves computed, 75 for 64 pivot steps with
+// two barriers each.  128 complex FP32 rows on 512 subdomains (two rounds) 86 us
+// against 131 and 305.  A factorisation of 32^3 in 8 subdomains, which little
+// else but this chain keeps waiting, 6.7 ms in FP64 and 4.2 in FP32 (7.2, 5.4).
 // stats[2 (sub max_sz + k) + 1] receives the bits of max 1 / |pivot|^2.
 template <typename R>
 __global__ void __launch_bounds__(64 * GjBlock<R>::WAVES)
@@ -366,40 +407,72 @@ gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
   const int nblk = nb * TILE / 16;
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
   const int wv = threadIdx.x >> 6;
-  auto at = [&](int bi, int bj) { return A + 16 * (bi * LD + bj); };
-  for (int i = threadIdx.x; i < nb * nb * TILE * TILE; i += 64 * WAVES) {
-    const int t = i / (TILE * TILE), e = i % (TILE * TILE);
-    const int ti = t / nb, tj = t % nb;
-    if (ti > tj) continue;
+  auto at = [&](int bi, int bj) { return Block<R>{A + 16 * (bi * LD + bj), LD}; };
+  // tiles on and above the diagonal, all loads in flight at once
+  constexpr int TT = TILE * TILE, NTHR = 64 * WAVES, TILES = GjBlock<R>::NBT * (GjBlock<R>::NBT + 1) / 2;
+  constexpr int NLOAD = (TILES * TT + NTHR - 1) / NTHR;
+  T v[NLOAD];
+#pragma unroll
+  for (int n = 0; n < NLOAD; ++n) {
+    const int i = n * NTHR + threadIdx.x, t = i / TT;
+    const int tj = (t > 0) + (t > 2) + (t > 5), ti = t - tj * (tj + 1) / 2;
+    v[n] = tj < nb ? base[tile_off(kb0 + ti, kb0 + tj, sd.nt) + i % TT] : czero<T>();
+  }
+#pragma unroll
+  for (int n = 0; n < NLOAD; ++n) {
+    const int i = n * NTHR + threadIdx.x, t = i / TT, e = i % TT;
+    const int tj = (t > 0) + (t > 2) + (t > 5), ti = t - tj * (tj + 1) / 2;
     const int row = ti * TILE + ((e >> 2) & 31), col = tj * TILE + (e >> 7) * 4 + (e & 3);
-    const T v = base[tile_off(kb0 + ti, kb0 + tj, sd.nt) + e];
-    A[row * LD + col] = v;
-    if (ti < tj) A[col * LD + row] = v;
+    if (tj >= nb) continue;
+    A[row * LD + col] = v[n];
+    if (ti < tj) A[col * LD + row] = v[n];
   }
   __syncthreads();
   R mag_min = INFINITY;    // smallest |pivot|^2 seen (wave 0)
   bool bad = false;
   const int live = sd.p - TILE * kb0;     // pivots that are not padding
-  for (int b = 0; b < nblk; ++b) {
-    // wave 0: the diagonal block; the rest: block column b - 1 <- -A_ik A_kk^{-1}
-    if (wv == 0) invert16<R>(at(b, b), LD, live - 16 * b, mag_min, bad);
-    else if (b > 0)
-      for (int i = wv - 1; i < nblk; i += WAVES - 1)
-        if (i != b - 1) block_product<R, false, true>(at(i, b - 1), at(i, b - 1), at(b - 1, b - 1), LD);
+  for (int b = -1; b < nblk; ++b) {
+    // block row b <- A_bb^{-1} A_bj; column b - 1 is not written yet, it is
+    // minus the transposed row b - 1 here
+    for (int j = wv; j < nblk && b >= 0; j += WAVES) {
+      if (j == b) continue;
+      if (j == b - 1) block_product<R, false, true>(at(b, j), at(b, b), at(j, b));
+      else block_product<R, false, false>(at(b, j), at(b, b), at(b, j));
+    }
     __syncthreads();
-    for (int j = wv; j < nblk; j += WAVES)
-      if (j != b) block_product<R, false, false>(at(b, j), at(b, b), at(b, j), LD);
-    __syncthreads();
-    for (int t = wv; t < (nblk - 1) * (nblk - 1); t += WAVES) {
-      int i = t / (nblk - 1), j = t % (nblk - 1);
-      i += i >= b;
-      j += j >= b;
-      block_product<R, true, false>(at(i, j), at(i, b), at(b, j), LD);
+    // wave 0: the next diagonal block and its inverse; the rest: the other
+    // blocks of the update, one of (i, j) and (j, i) each, for b - 1 the one in
+    // row b - 1.  Column b keeps its old values, which the update reads.
+    const bool ahead = b + 1 < nblk;
+    if (ahead && wv == 0) {
+      __builtin_amdgcn_s_setprio(3);
+      if (b >= 0)
+        block_product<R, true, false>(at(b + 1, b + 1), at(b + 1, b), at(b, b + 1));
+      invert16<R>(at(b + 1, b + 1).p, LD, live - 16 * (b + 1), mag_min, bad);
+      __builtin_amdgcn_s_setprio(0);
+    } else if (b >= 0) {
+      const int first = ahead ? wv - 1 : wv, step = ahead ? WAVES - 1 : WAVES;
+      for (int t = first; t < nblk * (nblk - 1) / 2; t += step) {
+        int j = 0;
+        while ((j + 1) * (j + 2) / 2 <= t) ++j;
+        int i = t - j * (j + 1) / 2;       // i <= j of the nblk - 1 blocks but b
+        i += i >= b;
+        j += j >= b;
+        if (ahead && i == b + 1 && j == b + 1) continue;
+        if (j == b - 1) {
+          j = i;
+          i = b - 1;
+        }
+        block_product<R, true, false>(at(i, j), at(i, b), at(b, j),
+                                      i == j ? nullptr : at(j, i).p,
+                                      (i <= b) == (j <= b) ? (R)1 : (R)-1);
+      }
     }
     __syncthreads();
   }
-  for (int i = wv; i < nblk - 1; i += WAVES)
-    block_product<R, false, true>(at(i, nblk - 1), at(i, nblk - 1), at(nblk - 1, nblk - 1), LD);
+  // the last block column: the transposed last row
+  for (int i = threadIdx.x; i < (nblk - 1) * 256; i += 64 * WAVES)
+    at(i >> 8, nblk - 1)((i >> 4) & 15, i & 15) = at(nblk - 1, i >> 8)(i & 15, (i >> 4) & 15);
   __syncthreads();
   for (int i = threadIdx.x; i < nb * nb * TILE * TILE; i += 64 * WAVES) {
     const int t = i / (TILE * TILE), e = i % (TILE * TILE);
