@@ -28,8 +28,8 @@
 // A_JI = -A_IJ^T otherwise.  So only the tiles with I <= J are kept up to date,
 // which halves the trailing update that carries almost all the work, and the
 // last pivot block writes the mirror tiles (with every tile updated, 96^3 in 64
-// subdomains took 180 ms a factorisation in complex128, now 99; 160^3 in 512
-// took 224 ms in complex64, now 126).
+// subdomains took 180 ms a factorisation in complex128, now 90; 160^3 in 512
+// took 224 ms in complex64, now 113).
 #include <type_traits>
 #include <utility>
 
@@ -390,8 +390,8 @@ __device__ inline void block_product(Block<R> D, Block<R> X, Block<R> Y, C<R>* m
 // 64 complex FP64 rows 28 us a call: 64 pivots of 0.27 (about 25 dependent FP64
 // instructions each), the rest are products, loads and stores; 33 with the next
 // inverse after the update and both halves computed, 75 for 64 pivot steps with
-// two barriers each.  128 complex FP32 rows on 512 subdomains (two rounds) 86 us
-// against 131 and 305.  A factorisation of 32^3 in 8 subdomains, which little
+// two barriers each.  128 complex FP32 rows on 256 subdomains, beside the other
+// 256's products, 86 us against 131 and 305.  A factorisation of 32^3 in 8 subdomains, which little
 // else but this chain keeps waiting, 6.7 ms in FP64 and 4.2 in FP32 (7.2, 5.4).
 // stats[2 (sub max_sz + k) + 1] receives the bits of max 1 / |pivot|^2.
 template <typename R>
@@ -516,7 +516,7 @@ template <typename R> struct TileMma;
 // to the same k.  Y is kept split: per half tile six blocks (pieces 1 - 3 of the
 // real part, of the imaginary part) of one 16-byte group per lane.
 template <> struct TileMma<float> {
-  static constexpr int OPERAND_BYTES = 12 * 64 * 16;
+  static constexpr int OPERAND_BYTES = 12 * 64 * 16, NX = 8;
   f32x16 accR, accI;
   float4 x[8];
   float2 y[4];
@@ -556,8 +556,8 @@ template <> struct TileMma<float> {
       o[(3 + q) * 128] = make_uint2(pi[q][0], pi[q][1]);
     }
   }
-  // next: the X tile to fetch as the registers of this one come free
-  __device__ void mac(const void* lds, const float2* __restrict__ next) {
+  // fetch(i0, i1) is called as x[i0 .. i1) comes free
+  template <typename F> __device__ void mac(const void* lds, F fetch) {
     const u32x4* Y = reinterpret_cast<const u32x4*>(lds) + (threadIdx.x & 63);
     const u32x4 sgn = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
 #pragma unroll
@@ -568,7 +568,7 @@ template <> struct TileMma<float> {
         split3(x[4 * hj + q].x, x[4 * hj + q].z, r1[q], r2[q], r3[q]);
         split3(x[4 * hj + q].y, x[4 * hj + q].w, i1[q], i2[q], i3[q]);
       }
-      fetch_x(next, 4 * hj, 4 * hj + 4);
+      fetch(4 * hj, 4 * hj + 4);
       const bf16x8 Xr1 = as_bf16x8(u32x4{r1[0], r1[1], r1[2], r1[3]});
       const bf16x8 Xr2 = as_bf16x8(u32x4{r2[0], r2[1], r2[2], r2[3]});
       const bf16x8 Xr3 = as_bf16x8(u32x4{r3[0], r3[1], r3[2], r3[3]});
@@ -607,7 +607,7 @@ template <> struct TileMma<float> {
 // 16-column halves, the real and imaginary parts of the result in separate
 // accumulators.  Y is kept as the tile with padded column groups (lds_tile).
 template <> struct TileMma<double> {
-  static constexpr int OPERAND_BYTES = LTILE * (int)sizeof(double2);
+  static constexpr int OPERAND_BYTES = LTILE * (int)sizeof(double2), NX = 16;
   f64x4 acc[2][2][2];
   double2 x[16], y[4];
   __device__ void zero() {
@@ -628,7 +628,7 @@ template <> struct TileMma<double> {
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[lds_entry(threadIdx.x + 256 * j)] = y[j];
   }
-  __device__ void mac(const void* lds, const double2* __restrict__ next) {
+  template <typename F> __device__ void mac(const void* lds, F fetch) {
     const double2* Y = reinterpret_cast<const double2*>(lds);
     const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
 #pragma unroll
@@ -647,7 +647,7 @@ template <> struct TileMma<double> {
           re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].y, -u.y, re, 0, 0, 0);
           im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ns].x, u.y, im, 0, 0, 0);
         }
-      fetch_x(next, 2 * q, 2 * q + 2);
+      fetch(2 * q, 2 * q + 2);
     }
   }
   template <typename F> __device__ void visit(F f) const {
@@ -670,7 +670,9 @@ template <> struct TileMma<double> {
 //   W_J,t  the new A_kJ = A_kk^{-1} A_kJ (the update's right operand) to its
 //          place for J after the pivot block; for J before it, whose place
 //          holds the transposed tile (J, kb0 + t), to both.
-// The last pivot block of a plane also writes the tile's mirror.
+// The last pivot block of a plane also writes the tile's mirror.  All loads of a
+// wave's tile are in flight at once: 26 us a call (29 with four) on 32
+// subdomains of 800 rows in FP64, a factorisation of 160^3 in FP32 118 ms (122).
 template <typename R>
 __global__ void __launch_bounds__(64 * GjBlock<R>::NBT)
 gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
@@ -692,11 +694,14 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   if (wv < nb) {
     const T* g = base + (after ? tile_off(kb0 + wv, J, sd.nt) : tile_off(J, kb0 + wv, sd.nt));
     T* sY = reinterpret_cast<T*>(lds[wv]);
-#pragma unroll 4
+    T ld[TT / 64];       // all loads of the tile in flight
+#pragma unroll
+    for (int i = 0; i < TT / 64; ++i) ld[i] = g[i * 64 + lane];
+#pragma unroll
     for (int i = 0; i < TT / 64; ++i) {
       // entry e of the tile: row r, column c
       const int e = i * 64 + lane, r = (e >> 2) & 31, c = (e >> 7) * 4 + (e & 3);
-      T v = g[e];
+      T v = ld[i];
       Cs[wv * TT + (after ? in_tile(c, r) : e)] = v;
       if (!after) {        // eliminated before: A_kJ = -A_Jk^T
         v.x = -v.x;
@@ -723,10 +728,12 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   mm.zero();
   const T* D = base + tile_off(kb0 + wv, kb0, sd.nt);
   mm.fetch_x(D);
-  for (int u = 0; u < nb; ++u) {
-    mm.mac(lds[u], D + min(u + 1, nb - 1) * TT);
+  for (int u = 0; u < nb - 1; ++u) {
+    const T* next = D + (u + 1) * TT;
+    mm.mac(lds[u], [&](int i0, int i1) { mm.fetch_x(next, i0, i1); });
     asm volatile("" ::: "memory");      // keeps the fetch in this iteration
   }
+  mm.mac(lds[nb - 1], [](int, int) {});
   T* lo = base + tile_off(kb0 + wv, J, sd.nt);     // its place, or the mirror of it
   T* up = base + tile_off(J, kb0 + wv, sd.nt);
   mm.visit([&](int row, int col, T v) {
@@ -749,7 +756,12 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
 // On 512 subdomains of 576-row planes in FP32 a call takes 398 us (429 with one
 // wave per work-group that staged and split W for itself), of which the tiles'
 // own traffic is 170 and the matrix unit 134; on 64 of 800-row planes in FP64
-// 171, of which either is about 100.  Four columns per work-group, to amortise
+// 171, of which either is about 100.  The tile itself is fetched into the
+// registers that the last products free, and nothing is fetched past the last
+// pivot tile: with two halves of the subdomains side by side, 32 of 800 rows in
+// FP64 take 82 us a call (89 with a fetch in every step and the tile read after
+// the products), a factorisation of 96^3 in FP64 90 ms (96), of 160^3 in FP32
+// 113 (118).  Four columns per work-group, to amortise
 // its start, changed nothing in FP32 and spilled in FP64 (206).
 constexpr int NXCD = 8;
 constexpr int UW = 4;      // waves, row tiles, of an update work-group
@@ -793,19 +805,27 @@ gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>
   mm.zero();
   mm.fetch_y(Ws);
   if (live) mm.fetch_x(Cs);
-  for (int u = 0; u < nb; ++u) {
+  int u = 0;
+  for (; u < nb - 1; ++u) {
     mm.stage_y(lds[u & 1]);
     __syncthreads();
-    mm.fetch_y(Ws + min(u + 1, nb - 1) * wstep);
-    if (live) mm.mac(lds[u & 1], Cs + min(u + 1, nb - 1) * TT);
+    mm.fetch_y(Ws + (u + 1) * wstep);
+    const T* next = Cs + (u + 1) * TT;
+    if (live) mm.mac(lds[u & 1], [&](int i0, int i1) { mm.fetch_x(next, i0, i1); });
     asm volatile("" ::: "memory");      // keeps the fetches in this iteration
   }
-  T cv[16];
-  if (live) {
-    int n = 0;
-    mm.visit([&](int row, int col, T) { cv[n++] = Aij[in_tile(row, col)]; });
-  }
+  mm.stage_y(lds[u & 1]);
+  __syncthreads();
   if (!live) return;
+  // the last products: the tile itself comes into the registers they free
+  T cv[16];
+  mm.mac(lds[u & 1], [&](int i0, int i1) {
+    int n = 0;
+    mm.visit([&](int row, int col, T) {
+      if (n >= i0 * 16 / M::NX && n < i1 * 16 / M::NX) cv[n] = Aij[in_tile(row, col)];
+      ++n;
+    });
+  });
   int n = 0;
   mm.visit([&](int row, int col, T v) {
     const T w = csub(cv[n], v);
