@@ -399,6 +399,55 @@ __device__ inline bool item_map(int nitems, int ncg, int& it, int& cg) {
   return it < nitems;
 }
 
+// Operand-buffer rows of an item's 4-row groups, for groups asked for in
+// increasing order, in pairs (segments are whole pairs): the operand's columns
+// are one run over all segments, so the FP32 kernel keeps loading across their
+// ends.  Lane i of the wave holds segment base + i; nothing waits for memory
+// between two segments but once in 64.
+//
+// Projection and expansion of a plane step, in brackets with a pipeline started
+// and drained for every segment: 61 x 47 x 53 in 18 subdomains, 5 right-hand
+// sides 20.0 (22.4) us, 96^3 in 64, 32 44.3 (48.1), 120^3 in 216, 32 71.6
+// (79.0), 160^3 in 512, 32 152 (160).  The FP64 kernel, which starts its short
+// loads again for each segment, was no faster this way up to 16 columns and
+// slower with 32 (94 against 78 on 96^3).
+template <int MODE> struct SegmentRows {
+  const BlrItem& item;
+  const int* lists;
+  int end, off;               // lane's segment: first group after it, row - 4 group
+  int base = 0, cur_end = 0, cur_off = 0;
+  __device__ SegmentRows(const BlrItem& it, const int* l, int first) : item(it), lists(l) {
+    if (MODE == 0) {
+      cur_off = item.brow;
+      return;
+    }
+    window();
+    advance(first);
+  }
+  __device__ void window() {
+    const int i = min(base + (int)(threadIdx.x & 63), item.nseg - 1);
+    const int4 seg = *reinterpret_cast<const int4*>(lists + item.list_off + 4 * i);
+    end = (seg.x + seg.z) >> 2;
+    off = seg.y - seg.x;
+  }
+  // to the segment of the group, which is not past the last one
+  __device__ void advance(int group) {
+    unsigned long long after = __ballot(end > group);
+    while (after == 0 && base + 64 < item.nseg) {
+      base += 64;
+      window();
+      after = __ballot(end > group);
+    }
+    const int sg = after ? __builtin_ctzll(after) : 63;
+    cur_end = __builtin_amdgcn_readlane(end, sg);
+    cur_off = __builtin_amdgcn_readlane(off, sg);
+  }
+  __device__ int row(int group) {
+    if (MODE == 1 && group >= cur_end) advance(group);
+    return cur_off + 4 * group;
+  }
+};
+
 // Complex FP32 on the bf16 instruction (32x32x16) with exactly split operands,
 // as the dense plane products: every FP32 value of both operands is split
 // into three bf16 pieces and six piece products form each real product, so
@@ -409,8 +458,8 @@ __device__ inline bool item_map(int nitems, int ncg, int& it, int& cg) {
 // stored operand: lane (n = lane % 32, g = lane / 32) holds the operand
 // entries (row n, k = 4 q + 2 g + e) and the t or T values (k = 4 q + 2 g + e,
 // column n), value i = 2 q + e of both instruction operands referring to the
-// same k.  A run of 4 m + 2 groups ends with a step whose last two groups are
-// zeroed in the stored operand.
+// same k.  A wave's 4 m + 2 groups end with a step whose last two are zeroed in
+// the stored operand.
 template <int MODE, int KS, typename Z>
 __global__ void __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(2)))
 blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ bsubs,
@@ -439,18 +488,24 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
     accR[j] = 0.f;
     accI[j] = 0.f;
   }
-  // groups kq .. kq + 3 of the run [q0, q1) whose group q0 starts at
-  // operand-buffer row rbase0; groups past the end repeat the last one with
-  // the stored operand zeroed
-  auto load = [&](int kq, int q0, int q1, int rbase0, float4 (&a)[4], float2 (&b)[8]) {
+  // the wave's groups [w0, w1) of the operand's K / 4
+  const int w0 = 2 * (item.K / 8 * wv / KS), w1 = 2 * (item.K / 8 * (wv + 1) / KS);
+  SegmentRows<MODE> rows(item, lists, w0);
+  // groups kq .. kq + 3; a pair past the end repeats the last one with the
+  // stored operand zeroed
+  auto load = [&](int kq, float4 (&a)[4], float2 (&b)[8]) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int gq = min(kq + q, q1 - 1);
-      a[q] = A[((long long)gq * item.mpad + item.row0 + n) * 2 + g];
-      if (kq + q >= q1) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int h = 0; h < 2; ++h) {
+      const int kp = min(kq + 2 * h, w1 - 2), rbase = rows.row(kp);
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
-        b[2 * q + e] = btc[(long long)(rbase0 + 4 * (gq - q0) + 2 * g + e) * s16 + colb];
+      for (int i = 0; i < 2; ++i) {
+        const int q = 2 * h + i;
+        a[q] = A[((long long)(kp + i) * item.mpad + item.row0 + n) * 2 + g];
+        if (kq + q >= w1) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          b[2 * q + e] = btc[(long long)(rbase + 4 * i + 2 * g + e) * s16 + colb];
+      }
     }
   };
   auto mma = [&](const float4 (&a)[4], const float2 (&b)[8]) {
@@ -492,35 +547,20 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
     ORAS_BX3(Ar2, Ai2, Ni2, Br2, Bi2)
 #undef ORAS_BX3
   };
-  // one run of groups [q0, q1): the next 16-k step is fetched while the
-  // current one feeds the products (loads past the end stay in bounds)
-  auto run = [&](int q0, int q1, int rbase0) {
+  // the next 16-k step is fetched while the current one feeds the products
+  if (w0 < w1) {
     float4 sa[4];
     float2 sb[8];
-    load(q0, q0, q1, rbase0, sa, sb);
-    for (int kq = q0; kq < q1; kq += 4) {
+    load(w0, sa, sb);
+    for (int kq = w0; kq < w1; kq += 4) {
       float4 ca[4];
       float2 cb[8];
 #pragma unroll
       for (int q = 0; q < 4; ++q) ca[q] = sa[q];
 #pragma unroll
       for (int j = 0; j < 8; ++j) cb[j] = sb[j];
-      load(kq + 4, q0, q1, rbase0, sa, sb);
+      if (kq + 4 < w1) load(kq + 4, sa, sb);
       mma(ca, cb);
-    }
-  };
-  // the wave's part of a run: groups [w0, w1) of the operand's K / 4
-  const int w0 = 2 * (item.K / 8 * wv / KS), w1 = 2 * (item.K / 8 * (wv + 1) / KS);
-  auto share = [&](int q0, int q1, int rbase0) {
-    const int a = max(q0, w0), b = min(q1, w1);
-    if (a < b) run(a, b, rbase0 + 4 * (a - q0));
-  };
-  if (MODE == 0) {
-    share(0, item.K >> 2, item.brow);
-  } else {
-    for (int sg = 0; sg < item.nseg; ++sg) {
-      const int4 seg = *reinterpret_cast<const int4*>(lists + item.list_off + 4 * sg);
-      share(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
     }
   }
   // the waves' sums in order; each wave adds up and stores NI of the 16 items.
@@ -746,7 +786,8 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
 // expansion, one wave in brackets: complex64 32^3 in 8 subdomains 14.7 (21.7)
 // us, 61 x 47 x 53 in 18 22.6 (27.7); complex128 15.1 (24.2) and 23.8 (33.6)); one
 // where there are enough (complex64 96^3 in 64 47.6 against 59.2, 160^3 in 512
-// 159 against 208; complex128 96^3 82.7 against 84.3).
+// 159 against 208; complex128 96^3 82.7 against 84.3; the complex64 figures with
+// a pipeline per segment).
 inline bool split_items(int count, int ncg) { return (long long)count * ncg < 1024; }
 
 template <typename R, typename Z> struct BlrStep;

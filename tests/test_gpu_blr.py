@@ -192,3 +192,20 @@ def test_refactor_after_compression_drops_the_compressed_form():
     assert torch.equal(S.apply_M(xd), F.apply_M(to_dev(x, F)))
     F.close()
     S.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 16), (26, 10), (24, 24)])
+def test_blr_many_segments(nx, ny):
+    """Dense blocks of 2 x 2 patches: 64, 65 and 144 operand segments per row
+    patch (a wave holds 64 of them at a time)."""
+    need_gpu()
+    w = wl.small_random((nx, ny, 6), npml=2, q=80.0, seed=15, parts=(1, 1, 1), overlap=1)
+    say(f"blr segments {nx}x{ny}")
+    S = setup(w, prec=1, parts=(1, 1, 1), overlap=1)
+    info = S.compress(0.0, 2)
+    assert info["lowrank"] == 0, info
+    x = rand_field((w.nz, w.ny, w.nx), 9, 16)
+    got = S.apply_M(to_dev(x, S)).cpu().numpy()
+    e = box_err(got, ooras.ORAS(oracle_fields(w), (1, 1, 1), 1).apply(x), (1, 1, 1), 1)
+    say(f"  per-box error {e:.2e}")
+    assert e < FP32_BOX, e
