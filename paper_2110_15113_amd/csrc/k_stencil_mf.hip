@@ -451,34 +451,38 @@ void launch_kind(const StencilMF<R>& op, const StencilTiles& tl, const X* x, con
   }
 }
 
-// The tallest tiles that give STENCIL_ITEMS work items, else the lowest ones: a
-// tile of TZ planes marches through TZ + 2, so low tiles cost more arithmetic,
-// but a small grid is one round of work-groups that lasts as long as its march.
-// 16 / 8 / 4 / 2 planes per tile: 96^3, 32 right-hand sides in single precision
-// (1728 work items of 16 planes) 548 / 566 / 606 / 733 us a call; 50 x 60 x 70,
-// 8 (280) 81 / 56 / 64 for the first three; 48^3, 1 in double (108) 45 with 4
-// (432) and 60 with 2.  At 384 items single precision takes 105 us with either
-// of the two heights, double 127 with the taller and 114 with the lower.
-const StencilTiles& tallest(const StencilTiles (&tl)[STENCIL_LISTS], int s) {
-  for (int q = 0; q < STENCIL_LISTS - 1; ++q)
-    if ((long long)tl[q].ntiles * ((s + 15) / 16) >= STENCIL_ITEMS) return tl[q];
-  return tl[STENCIL_LISTS - 1];
-}
-
-// The tiles of a call.  With fewer than ONE_LAUNCH work items in the launch
-// that covers the whole grid (in chunks of 16 right-hand sides), the PML-free
-// tiles go into the PML tiles' launch, their factors being 1: two launches one
-// after the other last as long as the longest work-groups of both.  One launch
-// against two: 32^3, 1 right-hand side in double (256 items) 30 / 40 us; 64^3,
-// 16 in single (512) 90 / 121; 72^3, 24 (405, and again for the last 8) 187 /
-// 289; 88^3, 8 (726) 98 / 126 with a PML of 3 nodes, 98 / 138 with 10.  Above,
-// the PML-free tiles' cheaper arithmetic counts: 96^3, 8 (864) 142 / 128 with
-// 3 nodes, 140 / 138 with 12; 96^3, 32 in double (1728) 482 / 459.
-constexpr int ONE_LAUNCH = 768;
-StencilTiles pick_tiles(const StencilTiles (&tl)[STENCIL_LISTS], int s) {
-  StencilTiles t = tallest(tl, s);
+// The tiles of a call: the tallest that give enough work items, else the lowest
+// ones.  A tile of TZ planes marches through TZ + 2, so low tiles cost more
+// arithmetic, but a small grid is one round of work-groups that lasts as long
+// as its march.
+//
+// FP64: enough is ONE_LAUNCH_TALL.  With fewer than ONE_LAUNCH work items in the
+// launch that covers the whole grid (in chunks of 16 right-hand sides), the
+// PML-free tiles go into the PML tiles' launch, their factors being 1: two
+// launches one after the other last as long as the longest work-groups of both.
+// One launch against two: 32^3, 1 right-hand side (256 items) 30 / 40 us; 64^3,
+// 16 (512) 79 / 121; 72^3, 24 (405, and again for the last 8) 228 / 326; 88^3, 8
+// (726) 155 / 197 with a PML of 10 nodes, 155 / 155 with 3; above, the PML-free
+// tiles' cheaper arithmetic counts: 96^3, 32 (1728) 482 / 459.  16 / 8 / 4 / 2
+// planes per tile: 50 x 60 x 70, 8 (280 of 16 planes) 102 / 68 / 84 for the first
+// three; 48^3, 1 (108) 45 with 4 (432 items) and 60 with 2.
+//
+// FP32: two launches always, as the PML tiles form their couplings in FP32 where
+// the PML-free tiles round each stiffness once: in one launch, solves of 30 000
+// to 250 000 nodes ended at the same residual with up to twice the error (5.3e-6
+// against 2.2e-6 relative).  Enough is STENCIL_ITEMS: 96^3, 32 (1728 items) 548 /
+// 566 / 606 / 733 us a call; 64^3, 16 (256) 171 / 127 / 125 / 138; 61 x 47 x 53,
+// 5 (192) 122 / 88 / 74 / 77.
+constexpr int ONE_LAUNCH = 768, ONE_LAUNCH_TALL = 400;
+template <typename R> StencilTiles pick_tiles(const StencilMF<R>& op, int s) {
+  constexpr bool F64 = sizeof(R) == 8;
+  int q = 0;
+  while (q < STENCIL_LISTS - 1 && (long long)op.tl[q].ntiles * ((s + 15) / 16) <
+                                      (F64 ? ONE_LAUNCH_TALL : STENCIL_ITEMS))
+    ++q;
+  StencilTiles t = op.tl[q];
   const int chunks = std::max((s + RHS_ALIGN - 1) / 16, 1);   // full ones, or the only one
-  if ((long long)t.ntiles * chunks < ONE_LAUNCH) t.nplain = 0;
+  if (F64 && (long long)t.ntiles * chunks < ONE_LAUNCH) t.nplain = 0;
   return t;
 }
 
@@ -516,7 +520,7 @@ template <typename R, typename Y>
 void launch_stencil_mf(const StencilMF<R>& op, const C<R>* x, const double2* b, Y* y, int nx,
                        int ny, int nz, int s, hipStream_t st) {
   static_assert(RHS_ALIGN == 8, "chunk widths cover multiples of 8");
-  const StencilTiles tl = pick_tiles(op.tl, s);
+  const StencilTiles tl = pick_tiles(op, s);
   launch_kind<R, false, false>(op, tl, x, b, y, nx, ny, nz, s, st);
   launch_kind<R, true, false>(op, tl, x, b, y, nx, ny, nz, s, st);
 }
@@ -524,7 +528,7 @@ void launch_stencil_mf(const StencilMF<R>& op, const C<R>* x, const double2* b, 
 template <typename R>
 void launch_stencil_mf_planar(const StencilMF<R>& op, const double2* x, double2* y, int nx, int ny,
                               int nz, int nrhs, hipStream_t st) {
-  const StencilTiles tl = pick_tiles(op.tl, nrhs);
+  const StencilTiles tl = pick_tiles(op, nrhs);
   launch_kind<R, false, true>(op, tl, x, nullptr, y, nx, ny, nz, nrhs, st);
   launch_kind<R, true, true>(op, tl, x, nullptr, y, nx, ny, nz, nrhs, st);
 }

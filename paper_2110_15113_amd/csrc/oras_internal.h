@@ -179,7 +179,7 @@ struct StencilTiles {
   int ntiles = 0, nplain = 0;
 };
 constexpr int STENCIL_LISTS = 4;   // tiles of 16, 8, 4 and 2 planes
-constexpr int STENCIL_ITEMS = 400; // a tiling with so many tiles serves any call
+constexpr int STENCIL_ITEMS = 512; // a tiling with so many tiles serves any call
 template <typename R> struct StencilMF {
   const typename R4<R>::type* f4;
   const R* fim;

@@ -81,8 +81,8 @@ def test_matrix_free_apply_after_set_m():
 
 
 # grids whose applies run tiles of 2, 4, 8 and 16 planes (8 x 8 columns, the
-# tallest with 400 work items): 25 x 2, 25 x 11 x 2, 36 x 5 x 3 and 64 x 3 x 3
-# tiles times chunks of 16
+# tallest with 512 work items in single precision, 400 in double): 25 x 2,
+# 25 x 11 x 2, 36 x 5 x 3 and 64 x 3 x 3 tiles times chunks of 16
 @pytest.mark.parametrize("n,nrhs", [((33, 34, 3), 1), ((33, 34, 41), 17), ((41, 42, 37), 33),
                                     ((57, 58, 33), 35)])
 def test_apply_of_caller_arrays(n, nrhs):
@@ -105,8 +105,8 @@ def test_apply_of_caller_arrays(n, nrhs):
 
 
 # 64 x 3 tiles, some of them PML-free, in 3 and in 4 chunks of 16: below and at
-# the 768 work items from which PML-free tiles have a launch of their own (the
-# 24 columns: one chunk of 16 and one of 8)
+# the 768 work items from which PML-free tiles have a launch of their own in
+# double precision (the 24 columns: one chunk of 16 and one of 8)
 @pytest.mark.parametrize("nrhs", [24, 48, 64])
 def test_apply_in_one_launch_or_two(nrhs):
     need_gpu()
@@ -119,3 +119,16 @@ def test_apply_in_one_launch_or_two(nrhs):
     for prec, bar in ((2, FP64_ROW), (1, FP32_ROW)):
         y = S.apply_A(to_dev(x, S), prec=prec)
         assert _row_err(y.cpu().numpy(), ref, scale) < bar
+
+
+# 33 and 48 columns: tiles of 16 planes, as 64 (lower tiles are PML-free more often)
+@pytest.mark.parametrize("nrhs", [33, 48])
+def test_fp32_apply_does_not_depend_on_the_block(nrhs):
+    """A column's single-precision result is bitwise the one it has in a block
+    of 64: small calls form the couplings no less exactly than large ones."""
+    need_gpu()
+    w = wl.small_random((57, 58, 33), npml=4, q=70.0, seed=65)
+    S = setup(w, prec=1)
+    x = to_dev(rand_field((w.nz, w.ny, w.nx), 64, 66), S)
+    big = S.apply_A(x, prec=1)
+    assert bool((S.apply_A(x[:nrhs].contiguous(), prec=1) == big[:nrhs]).all())
