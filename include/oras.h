@@ -302,15 +302,16 @@ oras_status oras_apply_M(oras_ctx ctx, const void* x_dev, void* y_dev, int nrhs)
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): oras_apply_A
  * with no allocation.  Same arguments, checks, kernels and results as
- * oras_apply_A (y_dev is written with y = A x, bitwise equal to it); the
- * staging it needs (x and y in the internal layout, and x rounded to complex64
- * for ORAS_C64: 16 + 16 (+ 8) bytes per node and padded right-hand side,
- * right-hand sides padded to a multiple of 8) lives in a fixed device array of
- * oras_noalloc_scratch_bytes() bytes (64 MiB) that every GPU the library runs
- * on holds until the process ends.  A larger request returns ORAS_E_ARG before
- * any device work.  All calls on one GPU share that GPU's array, so calls that
- * overlap on one GPU (several streams or host threads) race; calls ordered on
- * one stream do not. */
+ * oras_apply_A (y_dev is written with y = A x, bitwise equal to it).  A call
+ * whose x and y overlap (in place) needs staging (x and y in the internal
+ * layout, and x rounded to complex64 for ORAS_C64: 16 + 16 (+ 8) bytes per node
+ * and padded right-hand side, right-hand sides padded to a multiple of 8); it
+ * lives in a fixed device array of oras_noalloc_scratch_bytes() bytes (64 MiB)
+ * that every GPU the library runs on holds until the process ends.  A request
+ * whose staging would be larger returns ORAS_E_ARG before any device work,
+ * overlapping or not.  In-place calls on one GPU share that GPU's array, so
+ * those that run at the same time (several streams or host threads) race; calls
+ * ordered on one stream do not. */
 oras_status oras_apply_A_noalloc(oras_ctx ctx, const void* x_dev, void* y_dev, int nrhs, int prec);
 /* Size in bytes of the fixed staging array of oras_apply_A_noalloc. */
 size_t oras_noalloc_scratch_bytes(void);
