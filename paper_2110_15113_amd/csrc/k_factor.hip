@@ -666,7 +666,9 @@ template <> struct TileMma<double> {
 // The panels of one pivot block, for one tile index J outside it (one
 // work-group of NBT waves per (J, subdomain)): wave t writes
 //   C_J,t  the old A_Jk (tile t of the row, the update's left operand) to the
-//          plane's scratch (C tiles of all J, then W tiles),
+//          plane's scratch: nb tiles for each of the nt - nb tile indices
+//          outside the block, then the W tiles of the kb0 before it.  That is
+//          at most 2 (nt - nb) nb <= nt^2 / 2 tiles, so they fit where T was.
 //   W_J,t  the new A_kJ = A_kk^{-1} A_kJ (the update's right operand) to its
 //          place for J after the pivot block; for J before it, whose place
 //          holds the transposed tile (J, kb0 + t), to both.
@@ -687,8 +689,8 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
   if (J >= kb0 && J < kb0 + nb) return;
   const bool after = J > kb0, last = kb0 + nb == sd.nt;
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
-  T* Cs = tbuf + sd.t_off + (long long)J * NBT * TT;
-  T* Ws = Cs + (long long)sd.nt * NBT * TT;
+  T* Cs = tbuf + sd.t_off + (long long)(after ? J - nb : J) * nb * TT;
+  T* Ws = tbuf + sd.t_off + (long long)(sd.nt - nb + J) * nb * TT;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   M mm;
   if (wv < nb) {
@@ -796,10 +798,10 @@ gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>
   T* base = fac + sd.fac_off + (long long)k * sd.P * sd.P;
   T* Aij = base + tile_off(I, J, sd.nt);
   T* Aji = base + tile_off(J, I, sd.nt);
-  const T* Cs = tbuf + sd.t_off + (long long)I * NBT * TT;
+  const T* Cs = tbuf + sd.t_off + (long long)(I > kb0 ? I - nb : I) * nb * TT;
   // W_J: in its place after the pivot block, in the scratch before it
   const T* Ws = J > kb0 ? base + tile_off(kb0, J, sd.nt)
-                        : tbuf + sd.t_off + (long long)(sd.nt + J) * NBT * TT;
+                        : tbuf + sd.t_off + (long long)(sd.nt - nb + J) * nb * TT;
   const long long wstep = J > kb0 ? (long long)sd.nt * TT : TT;
   M mm;
   mm.zero();
@@ -836,11 +838,6 @@ gj_update_kernel(const SubDesc* subs, int nsub, int max_nt, int k, int kb0, C<R>
 }
 
 }  // namespace
-
-long long factor_scratch(int factor_prec, int nt) {
-  const int nbt = factor_prec == ORAS_C64 ? GjBlock<float>::NBT : GjBlock<double>::NBT;
-  return 2LL * nt * nbt * TILE * TILE;
-}
 
 template <typename R>
 void launch_factor_plane(const SubDesc* subs_dev, int nsub, int k, int max_nt, int max_sz,

@@ -899,7 +899,7 @@ oras_status oras_factor_subdomains_ex(oras_ctx c, const int parts[3], int overla
         fac_off += (long long)d.sz * d.P * d.P;
         lca_off += 27LL * d.sx * d.sy * d.sz;
         y_rows += (long long)d.sz * d.P;
-        t_off += std::max((long long)d.P * d.P, factor_scratch(factor_prec, d.nt));
+        t_off += (long long)d.P * d.P;
         tv_rows += d.P;
         max_sz = std::max(max_sz, d.sz);
         max_nt = std::max(max_nt, d.nt);

@@ -132,7 +132,7 @@ struct SubDesc {
   long long fac_off;     // complex offset of plane 0's inverse in the factor buffer
   long long lca_off;     // offset of the local coefficient array (27 * sx*sy*sz)
   long long y_off;       // offset of the local solution buffer (sz * P * s)  [in units of P*s]
-  long long t_off;       // offset of the scratch plane (P*P, at least factor_scratch) used while factoring
+  long long t_off;       // offset of the scratch plane (P*P) used while factoring
   long long tv_off;      // first plane row of the plane right-hand side (P rows)
 };
 
@@ -209,9 +209,6 @@ template <typename R>
 void launch_stencil_mf_planar(const StencilMF<R>& op, const double2* x, double2* y, int nx, int ny,
                               int nz, int nrhs, hipStream_t st);
 
-// Entries of a subdomain's scratch plane that the pivot panels need (C_J and W_J
-// of every tile index J, one tile per tile of the widest pivot block).
-long long factor_scratch(int factor_prec, int nt);
 // Factorisation, one plane for all subdomains.  stats (2 per subdomain plane,
 // zeroed before the first plane) receives the bits of max |S_k|^2 and of
 // max 1 / |pivot|^2 (non-negative doubles, whose bits order as their values).

@@ -33,3 +33,26 @@ def test_factor_edges(nx, ny):
         e = box_err(y, ref, parts, 0)
         say(f"  prec {prec}: {e:.2e}")
         assert np.isfinite(e) and e < bar
+
+
+# boxes of one tile and of five: pivot panels are packed into the scratch plane
+# of P x P entries a subdomain has for T, however few tiles a plane holds
+@pytest.mark.parametrize("n,parts", [((32, 32, 32), (16, 16, 16)), ((96, 96, 16), (8, 8, 4))])
+@pytest.mark.parametrize("prec", [1, 2])
+def test_factor_memory(n, parts, prec):
+    need_gpu()
+    import torch
+    w = wl.small_random(n, npml=1, q=50.0, seed=73)
+    S = setup(w, prec=prec)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    S.factor(parts, 0, prec)
+    used = before - torch.cuda.mem_get_info()[0]
+    box = [n[a] // parts[a] for a in range(3)]
+    P = -(-box[0] * box[1] // 32) * 32
+    entry = 8 if prec == 1 else 16
+    sub = (box[2] + 1) * P * P + 27 * box[0] * box[1] * box[2]    # factors, scratch, couplings
+    nsub = parts[0] * parts[1] * parts[2]
+    say(f"factor memory {n} {parts} prec {prec}: {used} of {nsub * sub * entry}")
+    # descriptors and statistics: well below 1 KB a subdomain, 2 MB pages
+    assert used <= nsub * (sub * entry + 1024) + (16 << 20)
