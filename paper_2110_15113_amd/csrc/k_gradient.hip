@@ -23,6 +23,8 @@
 // unit: 96^3 nodes, 32 right-hand sides take 0.58 ms (14.1 ms with one
 // thread per node gathering every product from memory, a pass for each of the
 // two parts and seven for the stiffness weights).
+#include <algorithm>
+
 #include "oras_internal.h"
 
 namespace oras {
@@ -37,13 +39,14 @@ template <bool WEIGHTS>
 __global__ void __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(3)))
 gradient_kernel(OpView V, const double2* __restrict__ qfac, const double* __restrict__ wtab,
                 int tab_count, double g0, double dg, const double2* __restrict__ u,
-                const double2* __restrict__ mu, int nrhs, double* __restrict__ gout) {
+                const double2* __restrict__ mu, int nrhs, unsigned first,
+                double* __restrict__ gout) {
   __shared__ double2 su[2][GN], sm[2][GN];
   const int tid = threadIdx.x;
   const long long n = (long long)V.nx * V.ny * V.nz;
-  // tiles in one grid dimension, x fastest (an axis may hold any share of 2^31 nodes)
-  const unsigned tx = (V.nx + GX - 1) / GX, ty = (V.ny + GY - 1) / GY;
-  const int i0 = blockIdx.x % tx * GX, j0 = blockIdx.x / tx % ty * GY, k0 = blockIdx.x / (tx * ty) * GZ;
+  // tiles in one grid dimension, x fastest
+  const unsigned tx = (V.nx + GX - 1) / GX, ty = (V.ny + GY - 1) / GY, tile = first + blockIdx.x;
+  const int i0 = tile % tx * GX, j0 = tile / tx % ty * GY, k0 = tile / (tx * ty) * GZ;
   // the halo nodes this thread fetches (-1: outside the grid, zero)
   long long src[GL];
 #pragma unroll
@@ -152,13 +155,19 @@ void launch_gradient(const OpView& op, const double2* qfac, const double* wtab, 
                      double g0, double dg, bool weights, const double2* u, const double2* mu,
                      int nrhs, double* g, hipStream_t st) {
   const long long tx = (op.nx + GX - 1) / GX, ty = (op.ny + GY - 1) / GY, tz = (op.nz + GZ - 1) / GZ;
-  const dim3 grid((unsigned)(tx * ty * tz));
-  if (weights)
-    hipLaunchKernelGGL((gradient_kernel<true>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
-                       g0, dg, u, mu, nrhs, g);
-  else
-    hipLaunchKernelGGL((gradient_kernel<false>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
-                       g0, dg, u, mu, nrhs, g);
+  // A launch holds fewer than 2^32 threads.  A grid of few nodes along two axes
+  // may need more: 3 x 5 x 2^25 nodes, a quarter of what a grid may have, take
+  // 2^24 tiles.
+  constexpr long long MAX_TILES = (1LL << 24) - 1;
+  for (long long first = 0; first < tx * ty * tz; first += MAX_TILES) {
+    const dim3 grid((unsigned)std::min(MAX_TILES, tx * ty * tz - first));
+    if (weights)
+      hipLaunchKernelGGL((gradient_kernel<true>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
+                         g0, dg, u, mu, nrhs, (unsigned)first, g);
+    else
+      hipLaunchKernelGGL((gradient_kernel<false>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
+                         g0, dg, u, mu, nrhs, (unsigned)first, g);
+  }
 }
 
 }  // namespace oras

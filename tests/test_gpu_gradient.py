@@ -26,3 +26,29 @@ def test_gradient_tiles(n, nrhs):
         g = S.gradient(to_dev(u, S), to_dev(mu, S), weights=weights).cpu().numpy()
         # the bar of the gradient's other comparisons with the oracle
         assert np.abs(g - ref).max() < 1e-11 * np.abs(ref).max()
+
+
+def test_gradient_of_more_tiles_than_a_launch_holds():
+    """A grid of few nodes along two axes has 2^24 tiles, 2^32 threads, in half
+    a billion nodes.  Its fields repeat along z, so away from the ends its
+    gradient repeats that of a short grid, tile by tile."""
+    need_gpu()
+    import torch
+    if torch.cuda.mem_get_info()[0] < 150e9:
+        pytest.skip("needs 150 GB of device memory")
+    from paper_2110_15113_amd import oras
+    period, ny, nx = 64, 5, 3
+    rng = np.random.default_rng(44)
+    fields = [rng.normal(size=(1, period, ny, nx)) + 1j * rng.normal(size=(1, period, ny, nx))
+              for _ in range(2)]
+    inner = []
+    for nz in (3 * period, 524300 * period):
+        say(f"gradient of {nx} x {ny} x {nz} nodes")
+        S = oras.Solver(0)
+        S.assemble(torch.full((nz, ny, nx), 2000.0, dtype=torch.float64, device=S.device), 20.0, 0, 40.0)
+        u, mu = (to_dev(f, S).repeat(1, nz // period, 1, 1) for f in fields)
+        g = S.gradient(u, mu, weights=True)
+        inner.append(g[period:-period].view(-1, period, ny, nx))
+        S.close()
+    assert bool((inner[0] != 0).all())
+    assert bool((inner[1] == inner[0]).all())
