@@ -275,6 +275,16 @@ template <int L> __device__ inline double lane_value(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Between LDS stores of a wave's lanes and accesses of the same bytes by its
+// other lanes.  A wave's LDS operations complete in order, so this costs no
+// wait: it keeps the compiler from moving them past each other, which the types
+// of the accesses or the address of a single lane may seem to allow.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int... I, typename F>
 __device__ inline void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
   (f(std::integral_constant<int, I>()), ...);
@@ -448,6 +458,7 @@ gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
       __builtin_amdgcn_s_setprio(3);
       if (b >= 0)
         block_product<R, true, false>(at(b + 1, b + 1), at(b + 1, b), at(b, b + 1));
+      wave_lds_sync();
       invert16<R>(at(b + 1, b + 1).p, LD, live - 16 * (b + 1), mag_min, bad);
       __builtin_amdgcn_s_setprio(0);
     } else if (b >= 0) {
@@ -714,13 +725,14 @@ gj_panel_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, C<R>* tbuf) {
     if constexpr (sizeof(R) == 4) {
       // the wave's own tile: columns into registers, then split in its place
       float2 v[4][4];
+      wave_lds_sync();
 #pragma unroll
       for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           v[w][j] = sY[lds_tile(16 * (w & 1) + 8 * (w >> 1) + 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1),
                                 lane & 31)];
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
 #pragma unroll
       for (int w = 0; w < 4; ++w) M::put(sY, w, v[w]);
     }
