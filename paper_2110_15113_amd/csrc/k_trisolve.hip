@@ -225,7 +225,7 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
                      float2* __restrict__ ybuf, Z* __restrict__ z, int nx, int ny, int s,
                      int s32) {
   using ZR = typename Comp<Z>::type;
-  __shared__ float red[KS][RT * 32][64];
+  __shared__ float red[KS][KS > 1 ? RT * 32 : 1][64];
   int sub, item;
   xcd_map(max_ng * ncc, sub, item);
   if (sub >= nsub) return;
@@ -241,7 +241,8 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
     A4[t] = reinterpret_cast<const float4*>(fac + sd.fac_off + (long long)k * P * P) +
             (long long)min(I0 + t, nt - 1) * nt * 512;
   const u32x4* B = tp + sd.tv_off * s32 * 3 / 4 + (long long)cc * (P / 16) * 6 * 64;
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wv = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int rr = lane & 31, g = lane >> 5;
   const int aoff = rr * 2 + g;
 
@@ -323,8 +324,8 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
 
   // accumulator item i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
   constexpr int NI = 16 / KS;      // items per wave and row tile
-  static_assert(KS > 1 && NI * KS == 16, "whole items per wave");
-  {
+  static_assert(NI * KS == 16, "whole items per wave");
+  if constexpr (KS > 1) {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -351,6 +352,10 @@ plane_gemm_x3_kernel(const SubDesc* __restrict__ subs, int nsub, int max_ng, int
     }
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
+      if constexpr (KS == 1) {
+        sum[j] = make_float2(accR[t][j], accI[t][j]);
+        continue;
+      }
       sum[j] = make_float2(red[0][t * 32 + NI * wv + j][lane], red[0][t * 32 + 16 + NI * wv + j][lane]);
 #pragma unroll
       for (int w = 1; w < KS; ++w) {
@@ -495,7 +500,7 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
   // of them a wave adds up and stores (waves from NE / EW on: none)
   using OT = typename std::conditional<(NC > 0), double2, double>::type;
   constexpr int NE = RS * NB * 4, EW = NE > KS ? NE / KS : 1;
-  __shared__ OT red[KS][NE][64];
+  __shared__ OT red[KS][KS > 1 ? NE : 1][64];
   int sub, item;
   xcd_map(max_rg * ncg, sub, item);
   if (sub >= nsub) return;
@@ -505,7 +510,8 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
   const int row0 = 16 * RS * (item / ncg), c0 = c0base + 16 * NC * (item % ncg);
   if (row0 >= sd.P) return;
   const int P = sd.P;
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wv = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int m = lane & 15, kk = lane >> 4;
   const bool im = (m & 1) != 0;
   // k-step g (4 columns) of the row tile starts at entry 128 g, its upper 16
@@ -572,16 +578,19 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
   }
   // result item e of a lane: 16-row half e / (4 NB), column block (e / 4) % NB,
   // i = e % 4: row kk + 4 i of the half, instruction column m
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
+  auto own = [&](int e) {
     const int rs = e / (4 * NB), nb = (e >> 2) % NB, i = e & 3;
-    if constexpr (NC > 0) red[wv][e][lane] = make_double2(acc[rs][2 * nb][i], acc[rs][2 * nb + 1][i]);
-    else red[wv][e][lane] = acc[rs][0][i];
+    if constexpr (NC > 0) return make_double2(acc[rs][2 * nb][i], acc[rs][2 * nb + 1][i]);
+    else return acc[rs][0][i];
+  };
+  if constexpr (KS > 1) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) red[wv][e][lane] = own(e);
   }
   OT* Yk = reinterpret_cast<OT*>(ybuf + (sd.y_off + (long long)k * P) * s + c0) + m;
   const int rstride = NC ? s : 2 * s;
   const bool final_plane = bwd || (k == sd.sz - 1);
-  if (wv * EW >= NE) {
+  if (KS > 1 && wv * EW >= NE) {
     __syncthreads();
     return;
   }
@@ -595,17 +604,22 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
       old[j] = Yk[(long long)(row0 + 16 * (e / (4 * NB)) + kk + 4 * (e & 3)) * rstride +
                   (NC && c0 + 16 * nb + m >= s ? 0 : 16 * nb)];
   }
-  __syncthreads();
+  if (KS > 1) __syncthreads();
 #pragma unroll
   for (int j = 0; j < EW; ++j) {
     const int e = wv * EW + j, nb = (e >> 2) % NB;
     const int row = row0 + 16 * (e / (4 * NB)) + kk + 4 * (e & 3);
     if (NC && c0 + 16 * nb + m >= s) continue;
-    OT val = red[0][e][lane];
+    OT val;
+    if constexpr (KS == 1) {
+      val = own(j);
+    } else {
+      val = red[0][e][lane];
 #pragma unroll
-    for (int w = 1; w < KS; ++w) {
-      if constexpr (NC > 0) val = cadd(val, red[w][e][lane]);
-      else val += red[w][e][lane];
+      for (int w = 1; w < KS; ++w) {
+        if constexpr (NC > 0) val = cadd(val, red[w][e][lane]);
+        else val += red[w][e][lane];
+      }
     }
     if (bwd) {
       if constexpr (NC > 0) val = csub(old[j], val);
@@ -625,24 +639,34 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
 // Columns in blocks of 32; what is left over takes 16 columns, 8 columns (parts
 // interleaved, no padding) or, for 24, a block of 32 with 8 columns unstored
 // (a second launch would read the factors again), in a launch of its own.
-// The split per work-group, measured per plane step with the one-wave,
-// unsplit kernel before it in brackets (160 x 160 x 100 in 320 subdomains and
-// 96^3 in 64 are large, 61 x 47 x 53 in 18 and 32^3 in 8 small):
-//   32 columns: bound by the matrix unit.  16 rows and 4 waves: 456 (497) us
-//   on 320 subdomains, 166 (228) on 64, 50 (98) on 18, 14 (42) on 8; 32 rows
-//   with 8 waves gave 453, 175, 64 and 21.
-//   8 or 16 columns: bound by the factor stream.  With 4 waves per SIMD or
-//   more to launch at 32 rows and 4 waves, that split: 16 columns 337 (358)
-//   and 122 (162) us, 8 columns 297 (321) and 110 (130); below that the chip
-//   would be partly idle, and 16 rows with 8 waves give 16 columns 37 (86) us
-//   on 18 subdomains against 42, 8 columns 30 (82) against 34, and on 8
-//   subdomains 11 (38) against 14.
+// The split per work-group (rows, waves), in us per plane step; in brackets the
+// one-wave kernel with 32 rows that this one replaced.  W counts the launch's
+// tiles of 16 rows.
+//   32 columns: bound by the matrix unit.
+//   * 32 rows, 4 waves in large launches, whose row halves share the t operand:
+//     128^3 in 512 boxes of 256 / 324 / 400 nodes a plane 175 / 277 / 366 (186 /
+//     319 / 413), with 64 columns 324 / 526 / 696 (331 / 530 / 699), 120^3 in 216
+//     290 (340); 16 rows 197 / 297 / 389, 371 / 592 / 767 and 299.
+//   * 16 rows, 4 waves below: 96^3 in 64 163 (227), 61 x 47 x 53 in 18 28 (60),
+//     32^3 in 8 13 (42); 32 rows 172, 32 and 19.
+//   * Short planes give fewer waves enough k-steps: 2 waves up to 6 row tiles
+//     (64^3 in 512 of 144 nodes 65 (80), 64 columns 112 (122); 4 waves 72, 128),
+//     one up to 2 (64^3 in 4096 of 36 nodes 97 (112), 4 waves 135; in 32768 of 4
+//     nodes 376 (384), 4 waves 449), with 32 rows in the largest launches (64
+//     columns 185 (185) and 647 (630); 16 rows 201 and 685).
+//   8 or 16 columns: bound by the factor stream.  With 4 waves per SIMD or more
+//   to launch at 32 rows and 4 waves, that split (120^3 in 216 225 (247) with 16
+//   columns, 201 (217) with 8); below that 16 rows and 8 waves (61 x 47 x 53 in 18
+//   22 (59), 19 (55); 32^3 in 8 11 (39)); one wave of 16 rows for planes of up to
+//   2 row tiles (32768 boxes of 4 nodes 253 (251), 160 (195); 32 rows and 4 waves
+//   300, 216).
 void gemm_f64_dispatch(const OrasPlan& pl, int k, int bwd, const double2* fac,
                        const double2* tvbuf, double2* ybuf, double2* z, int nx, int ny, int s,
                        hipStream_t st) {
   const int nsub8 = (pl.nsub + NXCD - 1) / NXCD * NXCD;
   const int groups = s / RHS_ALIGN, full = groups / 4, rem = groups % 4;
-  const bool large = (long long)nsub8 * pl.max_nt * 4 >= 4 * 1024;
+  const long long rows16 = (long long)nsub8 * pl.max_nt * 2;
+  const bool large = rows16 >= 2048;
   auto launch = [&](auto nc, auto rs, auto ks, auto pf, int ncg, int c0base) {
     const int max_rg = pl.max_nt * 2 / rs();
     hipLaunchKernelGGL((plane_gemm_f64_kernel<nc(), rs(), ks(), pf()>),
@@ -655,13 +679,24 @@ void gemm_f64_dispatch(const OrasPlan& pl, int k, int bwd, const double2* fac,
   const integral_constant<int, 2> n2;
   const integral_constant<int, 4> n4;
   const integral_constant<int, 8> n8;
+  auto wide = [&](int ncg, int c0base) {
+    const long long w = rows16 * ncg;
+    if (pl.max_nt <= 2 && w >= 16384) launch(n2, n2, n1, n2, ncg, c0base);
+    else if (pl.max_nt <= 2 && w >= 2048) launch(n2, n1, n1, n2, ncg, c0base);
+    else if (pl.max_nt <= 6 && w >= 2048) launch(n2, n1, n2, n2, ncg, c0base);
+    else if (w >= 7168) launch(n2, n2, n4, n2, ncg, c0base);
+    else launch(n2, n1, n4, n4, ncg, c0base);
+  };
+  auto narrow = [&](auto nc, int c0base) {
+    if (pl.max_nt <= 2 && large) launch(nc, n1, n1, n2, 1, c0base);
+    else if (large) launch(nc, n2, n4, n2, 1, c0base);
+    else launch(nc, n1, n8, n2, 1, c0base);
+  };
   const int c0 = full * 32;
-  if (full > 0) launch(n2, n1, n4, n4, full, 0);
-  if (rem == 3) launch(n2, n1, n4, n4, 1, c0);
-  if (rem == 2 && large) launch(n1, n2, n4, n2, 1, c0);
-  if (rem == 2 && !large) launch(n1, n1, n8, n2, 1, c0);
-  if (rem == 1 && large) launch(n0, n2, n4, n2, 1, c0);
-  if (rem == 1 && !large) launch(n0, n1, n8, n2, 1, c0);
+  if (full > 0) wide(full, 0);
+  if (rem == 3) wide(1, c0);
+  if (rem == 2) narrow(n1, c0);
+  if (rem == 1) narrow(n0, c0);
 }
 
 template <typename Z>
@@ -677,20 +712,30 @@ void plane_step_f32(const OrasPlan& pl, int k, int bwd, const float2* fac, const
                      st, pl.subs, pl.nsub, nrb, ncc, k, bwd, lca, ybuf, tp, v, scale, nx, ny, s,
                      s32);
   if (ev) (void)hipEventRecord(ev[0], st);
-  // Two row tiles per work-group share each t piece they load, which pays
-  // while there are work-groups to spare; the k range goes over four waves
-  // either way (measured per plane step, with one wave and two row tiles in
-  // brackets: two tiles 295 (302) us on 160^3 in 512 subdomains, 128 (129) on
-  // 120^3 in 216, 78 (82) on 96^3 in 64; one tile 311, 132, 75, and on
-  // 61 x 47 x 53 in 18 subdomains 26 (49), on 32^3 in 8 11 (30)).
-  auto gemm = [&](auto rt) {
+  // Rows and waves per work-group (us per plane step; the whole k range in one
+  // wave and two row tiles, RT 2 KS 1, in brackets):
+  //   * Short planes in large launches: RT 2 KS 1.  A wave's share of the k range
+  //     would be less than the sums cost (64^3 in 4096 boxes of 36 nodes a plane
+  //     59 with RT 2 KS 4 (50), in 32768 of 4 nodes 330 (227), 128^3 in 512 of
+  //     256 nodes 81 (78); 324 nodes 127 (130)).
+  //   * Else four waves.  Two row tiles share each t piece they load, which pays
+  //     while there are work-groups to spare (160^3 in 512 295 (302), 120^3 in 216
+  //     128 (129)), or where t itself is too large to stay in an XCD's L2 beside
+  //     the factors (48^3 in one box, 64 columns, 1.8 MB of t: 113 (149), one tile
+  //     117); one tile otherwise (96^3 in 64 74 (83), two tiles 77; 61 x 47 x 53
+  //     in 18 16 (38), 32^3 in 8 11 (31)).
+  auto gemm = [&](auto rt, auto ks) {
     const int max_ng = (pl.max_nt + rt() - 1) / rt();
-    hipLaunchKernelGGL((plane_gemm_x3_kernel<Z, rt(), 4>), dim3((unsigned)(nsub8 * max_ng * ncc)),
-                       dim3(256), 0, st, pl.subs, pl.nsub, max_ng, ncc, k, bwd, fac, tp, ybuf, z,
-                       nx, ny, s, s32);
+    hipLaunchKernelGGL((plane_gemm_x3_kernel<Z, rt(), ks()>),
+                       dim3((unsigned)(nsub8 * max_ng * ncc)), dim3(64 * ks()), 0, st, pl.subs,
+                       pl.nsub, max_ng, ncc, k, bwd, fac, tp, ybuf, z, nx, ny, s, s32);
   };
-  if ((long long)nsub8 * pl.max_nt * ncc >= 2048) gemm(std::integral_constant<int, 2>());
-  else gemm(std::integral_constant<int, 1>());
+  using std::integral_constant;
+  const bool large = (long long)nsub8 * pl.max_nt * ncc >= 2048;
+  if (large && pl.max_nt <= 8) gemm(integral_constant<int, 2>(), integral_constant<int, 1>());
+  else if (large || pl.max_p * s32 * 12 >= 1 << 20)
+    gemm(integral_constant<int, 2>(), integral_constant<int, 4>());
+  else gemm(integral_constant<int, 1>(), integral_constant<int, 4>());
   if (ev) (void)hipEventRecord(ev[1], st);
 }
 

@@ -19,10 +19,10 @@ PADDED = 56
 
 
 @functools.lru_cache(maxsize=None)
-def reference(grid):
+def reference(grid, columns=PADDED):
     c = GRIDS[grid]
     w = wl.small_random(c["n"], npml=2, q=70.0, seed=31)
-    x = rand_field((w.nz, w.ny, w.nx), PADDED, 33)
+    x = rand_field((w.nz, w.ny, w.nx), columns, 33)
     return w, x, ooras.ORAS(oracle_fields(w), c["parts"], c["ov"]).apply(x)
 
 
@@ -50,3 +50,25 @@ def test_plane_products_c64(grid, nrhs):
     S = setup(w, prec=1, parts=c["parts"], overlap=c["ov"])
     y = S.apply_M(to_dev(x[:nrhs], S)).cpu().numpy()
     assert box_err(y, ref[:nrhs], c["parts"], c["ov"]) < FP32_BOX
+
+
+# planes of one row tile in 2048 boxes, of eight in 128, of eleven in one box
+# whose 256 columns of t are 1 MB: one and two waves, both row splits
+GRIDS.update(short=dict(n=(64, 64, 16), parts=(16, 16, 8), ov=0),
+             tiles=dict(n=(60, 60, 16), parts=(4, 4, 8), ov=0),
+             one=dict(n=(19, 18, 6), parts=(1, 1, 1), ov=0))
+
+
+@pytest.mark.parametrize("prec,bar", [(1, FP32_BOX), (2, FP64_BOX)])
+@pytest.mark.parametrize("grid,nrhs", [("short", 3), ("short", 16), ("short", 24), ("short", 128),
+                                       ("tiles", 64), ("tiles", 128), ("one", 256)])
+def test_plane_products_by_plane_size(grid, nrhs, prec, bar):
+    need_gpu()
+    say(f"plane products {grid} nrhs={nrhs} prec={prec}")
+    c = GRIDS[grid]
+    w, x, ref = reference(grid, 256 if grid == "one" else 128)
+    S = setup(w, prec=prec, parts=c["parts"], overlap=c["ov"])
+    y = S.apply_M(to_dev(x[:nrhs], S)).cpu().numpy()
+    e = box_err(y, ref[:nrhs], c["parts"], c["ov"])
+    say(f"  per-box error {e:.2e}")
+    assert e < bar
