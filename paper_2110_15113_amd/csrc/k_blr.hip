@@ -642,20 +642,20 @@ blr_gemm_x3_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ 
   }
 }
 
-// Complex FP64: 16x16x4 MFMA, 32 rows x NB blocks of 16 columns per work-group
-// of KS waves, each taking a KS-th of the operand's columns; the real and
-// imaginary parts of the result are separate accumulators.  The waves' sums
+// Complex FP64: 16x16x4 MFMA, 32 rows x 16 columns per work-group of KS waves,
+// each taking a KS-th of the operand's columns; the real and imaginary parts of
+// the result are separate accumulators.  The waves' sums
 // meet in LDS and each wave adds up and stores its share.
 // A[row = lane % 16][k = lane / 16], B[k = lane / 16][col = lane % 16];
 // result item t of lane l is row l / 16 + 4 t, column l % 16.
-template <int MODE, int KS, int NB>
+template <int MODE, int KS>
 __global__ void __launch_bounds__(64 * KS)
 blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__ bsubs,
                     const BlrItem* __restrict__ items, int nitems, int ncg, int k, int bwd,
                     const double2* __restrict__ astore, const int* __restrict__ lists,
                     double2* __restrict__ bt, double2* __restrict__ ybuf,
                     double2* __restrict__ z, int nx, int ny, int s, int s16) {
-  constexpr int RG = 2, NE = RG * NB * 4;      // 16-row groups; result items per lane
+  constexpr int RG = 2, NE = RG * 4;      // 16-row groups; result items per lane
   __shared__ double2 red[KS][KS > 1 ? NE : 1][64];
   int it, cg;
   if (!item_map(nitems, ncg, it, cg)) return;
@@ -668,41 +668,32 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
   const double2* A = astore + item.a_off;
   const int wv = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
-  const int c0 = 16 * NB * cg;
-  // columns at or beyond s16 read column s16 - 1 (in bounds; their results are dropped)
-  int colc[NB];
+  const int col = 16 * cg + m;            // below s16
+  f64x4 acc[RG][2];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) colc[nb] = min(c0 + 16 * nb + m, s16 - 1);
-  f64x4 acc[RG][NB][2];
-#pragma unroll
-  for (int q = 0; q < RG * NB * 2; ++q)
-    acc[q / (2 * NB)][(q >> 1) % NB][q & 1] = f64x4{0, 0, 0, 0};
+  for (int q = 0; q < RG * 2; ++q) acc[q >> 1][q & 1] = f64x4{0, 0, 0, 0};
   // one 4-row group: lane kk takes operand row 4 kq + kk
-  auto load = [&](int kq, int rbase, double2 (&bv)[NB], double2 (&a)[RG]) {
-    const long long row = rbase + kk;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) bv[nb] = btc[row * s16 + colc[nb]];
+  auto load = [&](int kq, int rbase, double2& bv, double2 (&a)[RG]) {
+    bv = btc[(long long)(rbase + kk) * s16 + col];
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg)
       a[rg] = A[((long long)kq * item.mpad + item.row0 + 16 * rg + m) * 4 + kk];
   };
-  auto mma = [&](const double2 (&bv)[NB], const double2 (&a)[RG]) {
+  auto mma = [&](const double2& bv, const double2 (&a)[RG]) {
 #pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        f64x4 &re = acc[rg][nb][0], &im = acc[rg][nb][1];
-        re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv[nb].x, re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv[nb].y, im, 0, 0, 0);
-        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[rg].y, bv[nb].y, re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].y, bv[nb].x, im, 0, 0, 0);
-      }
+    for (int rg = 0; rg < RG; ++rg) {
+      f64x4 &re = acc[rg][0], &im = acc[rg][1];
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv.x, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].x, bv.y, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[rg].y, bv.y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rg].y, bv.x, im, 0, 0, 0);
+    }
   };
   // two groups in flight in two register sets (runs are multiples of 8 rows:
   // an even number of groups; nothing conditional)
   auto run = [&](int q0, int q1, int rbase0) {
-    double2 b0[NB], b1[NB], a0[RG], a1[RG];
-    auto ld = [&](int kq, double2 (&bv)[NB], double2 (&a)[RG]) {
+    double2 b0, b1, a0[RG], a1[RG];
+    auto ld = [&](int kq, double2& bv, double2 (&a)[RG]) {
       const int g = min(kq, q1 - 1);
       load(g, rbase0 + 4 * (g - q0), bv, a);
     };
@@ -734,11 +725,8 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
       share(seg.x >> 2, (seg.x + seg.z) >> 2, seg.y);
     }
   }
-  // result item e of a lane: row group e / (4 NB), column block (e / 4) % NB, t = e % 4
-  auto own = [&](int e) {
-    return make_double2(acc[e / (4 * NB)][(e >> 2) % NB][0][e & 3],
-                        acc[e / (4 * NB)][(e >> 2) % NB][1][e & 3]);
-  };
+  // result item e of a lane: row group e / 4, t = e % 4
+  auto own = [&](int e) { return make_double2(acc[e >> 2][0][e & 3], acc[e >> 2][1][e & 3]); };
   if (KS > 1) {
 #pragma unroll
     for (int e = 0; e < NE; ++e) red[wv][KS > 1 ? e : 0][lane] = own(e);
@@ -752,7 +740,7 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
 #pragma unroll
   for (int j = 0; j < NE / KS; ++j) {
     const int e = NE / KS * wv + j;
-    const int lr = 16 * (e / (4 * NB)) + kk + 4 * (e & 3), col = c0 + 16 * ((e >> 2) % NB) + m;
+    const int lr = 16 * (e >> 2) + kk + 4 * (e & 3);
     if (col >= s) continue;
     double2 val;
     if constexpr (KS == 1) {
@@ -783,11 +771,14 @@ blr_gemm_f64_kernel(const SubDesc* __restrict__ subs, const BlrSub* __restrict__
 
 // Waves per work-group of a launch: four where the items are few, so that the
 // chip is not waiting for single waves' chains (per plane step, projection and
-// expansion, one wave in brackets: complex64 32^3 in 8 subdomains 14.7 (21.7)
-// us, 61 x 47 x 53 in 18 22.6 (27.7); complex128 15.1 (24.2) and 23.8 (33.6)); one
-// where there are enough (complex64 96^3 in 64 47.6 against 59.2, 160^3 in 512
-// 159 against 208; complex128 96^3 82.7 against 84.3; the complex64 figures with
-// a pipeline per segment).
+// expansion, one wave in brackets: complex64 32^3 in 8 subdomains 14 (20) us,
+// 61 x 47 x 53 in 18 18 (23); complex128 14 (22) and 18 (29)); one where there are
+// enough (complex64 96^3 in 64 43 against 51, 160^3 in 512 159 against 208;
+// complex128 64^3 in 512, 8 x 8 patches 49 against 54).  The count is that of the
+// launch, empty items included: eight times the items of the busiest XCD, which
+// is what the launch waits for, also where few subdomains leave XCDs empty (36 x
+// 36 x 20 in one box, 4 x 4 patches, complex128 25 by this rule, 27 with four
+// waves, 30 with one).
 inline bool split_items(int count, int ncg) { return (long long)count * ncg < 1024; }
 
 template <typename R, typename Z> struct BlrStep;
@@ -827,28 +818,21 @@ template <> struct BlrStep<double, double2> {
                        0, st, pl.subs, pl.bsubs, pl.lists, k, bwd, lca, ybuf, bt, v, scale, nx, ny,
                        s, s16);
     if (ev) (void)hipEventRecord(ev[0], st);
-    // one block of 16 columns per work-group, two where there are two: the
-    // operand is then read once for both
-    const bool two = s > 16;
-    const int ncg = two ? (s + 31) / 32 : 1;
+    // 16 columns per work-group: with 32, which read the operand once for both
+    // halves, 33 to 48 columns multiplied 64, and few items left SIMDs idle (per
+    // plane step 96^3 in 64 boxes, 32 columns 78.5 us against 77.0, 40 columns
+    // 128 against 95; 64^3 in 64 56 against 48 and 74 against 55; only 64 columns
+    // of 64^3 in 512 boxes with 4 x 4 patches gained, 143 against 153)
+    const int ncg = (s + 15) / 16;
     auto gemm = [&](auto mode, int first, int count) {
       if (count == 0) return;
-      auto launch = [&](auto ks, auto nb) {
-        hipLaunchKernelGGL((blr_gemm_f64_kernel<mode(), ks(), nb()>),
-                           dim3((unsigned)(count * ncg)), dim3(64 * ks()), 0, st, pl.subs,
-                           pl.bsubs, pl.items + first, count, ncg, k, bwd, astore, pl.lists, bt,
-                           ybuf, z, nx, ny, s, s16);
+      auto launch = [&](auto ks) {
+        hipLaunchKernelGGL((blr_gemm_f64_kernel<mode(), ks()>), dim3((unsigned)(count * ncg)),
+                           dim3(64 * ks()), 0, st, pl.subs, pl.bsubs, pl.items + first, count, ncg,
+                           k, bwd, astore, pl.lists, bt, ybuf, z, nx, ny, s, s16);
       };
-      const std::integral_constant<int, 1> n1;
-      const std::integral_constant<int, 2> n2;
-      const std::integral_constant<int, 4> n4;
-      if (split_items(count, ncg)) {
-        if (two) launch(n4, n2);
-        else launch(n4, n1);
-      } else {
-        if (two) launch(n1, n2);
-        else launch(n1, n1);
-      }
+      if (split_items(count, ncg)) launch(std::integral_constant<int, 4>());
+      else launch(std::integral_constant<int, 1>());
     };
     gemm(std::integral_constant<int, 0>(), pl.p_first[k], pl.p_count[k]);
     gemm(std::integral_constant<int, 1>(), pl.e_first[k], pl.e_count[k]);

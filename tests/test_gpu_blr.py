@@ -209,3 +209,30 @@ def test_blr_many_segments(nx, ny):
     e = box_err(got, ooras.ORAS(oracle_fields(w), (1, 1, 1), 1).apply(x), (1, 1, 1), 1)
     say(f"  per-box error {e:.2e}")
     assert e < FP32_BOX, e
+
+
+@pytest.mark.parametrize("nrhs", [9, 40])
+@pytest.mark.parametrize("prec", [1, 2])
+def test_blr_many_boxes(prec, nrhs):
+    """128 boxes, whose projections and expansions are both launched with one
+    wave per item (from 1024 items on), one and several column groups, the last
+    one partial."""
+    need_gpu()
+    n, parts, ov, pmax, eps = (48, 48, 8), (8, 8, 2), 2, 4, 1e-3
+    w = wl.small_random(n, npml=2, q=60.0, seed=9, parts=parts, overlap=ov)
+    say(f"blr many boxes prec={prec} nrhs={nrhs}")
+    M = oblr.OrasBLR(oracle_fields(w), parts, ov, eps, pmax)
+    for k in range(M.subs[0].hi[2] - M.subs[0].lo[2]):
+        proj, exp = np.zeros(8), np.zeros(8)      # items of the boxes that share a die
+        for j, sol in enumerate(M.solvers):
+            r = sol.inv[k].rank
+            low = np.where((r >= 0) & ~np.eye(len(r), dtype=bool), r, 0).sum(axis=0)
+            proj[j % 8] += -(-low // 32).sum()
+            exp[j % 8] += len(r)
+        assert 8 * proj.max() >= 1024 and 8 * exp.max() >= 1024
+    S = setup(w, prec=prec, parts=parts, overlap=ov)
+    assert S.compress(eps, pmax)["lowrank"] > 0
+    x = rand_field((w.nz, w.ny, w.nx), nrhs, 17)
+    e = box_err(S.apply_M(to_dev(x, S)).cpu().numpy(), M.apply(x), parts, ov)
+    say(f"  per-box error {e:.2e}")
+    assert e < (BLR32_BOX * eps if prec == 1 else FP64_BOX), e
