@@ -15,8 +15,8 @@
 //
 // Both need, per node, the 27 sums over the right-hand sides of the products
 // of u and mu with their neighbours, and nothing else of u and mu.  A
-// work-group owns a 16 x 4 x 4 tile of nodes, keeps its 27 sums in registers
-// and streams the right-hand sides through LDS (tile and halo, two buffers,
+// work-group owns a 16 x 4 x 4 tile of nodes (4 x 8 x 8 where the grid has few
+// along x), keeps its 27 sums in registers and streams the right-hand sides through LDS (tile and halo, two buffers,
 // the next one's loads in flight), so u and mu are read once from memory and
 // the halo's share (2.5 times the tile) again from the caches.  Bound by the
 // 53 complex multiply-adds per node and right-hand side on the FP64 vector
@@ -31,16 +31,17 @@ namespace oras {
 
 namespace {
 
-constexpr int GX = 16, GY = 4, GZ = 4, GT = GX * GY * GZ;
-constexpr int GHX = GX + 2, GHY = GY + 2, GHZ = GZ + 2, GN = GHX * GHY * GHZ;
-constexpr int GL = (GN + GT - 1) / GT;      // halo nodes per thread
+constexpr int GT = 256;      // threads of a work-group, nodes of its GX x GY x GZ tile
 
-template <bool WEIGHTS>
+template <bool WEIGHTS, int GX, int GY, int GZ>
 __global__ void __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(3)))
 gradient_kernel(OpView V, const double2* __restrict__ qfac, const double* __restrict__ wtab,
                 int tab_count, double g0, double dg, const double2* __restrict__ u,
                 const double2* __restrict__ mu, int nrhs, unsigned first,
                 double* __restrict__ gout) {
+  static_assert(GX * GY * GZ == GT, "one node per thread");
+  constexpr int GHX = GX + 2, GHY = GY + 2, GHZ = GZ + 2, GN = GHX * GHY * GHZ;
+  constexpr int GL = (GN + GT - 1) / GT;      // halo nodes per thread
   __shared__ double2 su[2][GN], sm[2][GN];
   const int tid = threadIdx.x;
   const long long n = (long long)V.nx * V.ny * V.nz;
@@ -154,19 +155,26 @@ gradient_kernel(OpView V, const double2* __restrict__ qfac, const double* __rest
 void launch_gradient(const OpView& op, const double2* qfac, const double* wtab, int tab_count,
                      double g0, double dg, bool weights, const double2* u, const double2* mu,
                      int nrhs, double* g, hipStream_t st) {
-  const long long tx = (op.nx + GX - 1) / GX, ty = (op.ny + GY - 1) / GY, tz = (op.nz + GZ - 1) / GZ;
-  // A launch holds fewer than 2^32 threads.  A grid of few nodes along two axes
-  // may need more: 3 x 5 x 2^25 nodes, a quarter of what a grid may have, take
-  // 2^24 tiles.
-  constexpr long long MAX_TILES = (1LL << 24) - 1;
-  for (long long first = 0; first < tx * ty * tz; first += MAX_TILES) {
-    const dim3 grid((unsigned)std::min(MAX_TILES, tx * ty * tz - first));
-    if (weights)
-      hipLaunchKernelGGL((gradient_kernel<true>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
-                         g0, dg, u, mu, nrhs, (unsigned)first, g);
-    else
-      hipLaunchKernelGGL((gradient_kernel<false>), grid, dim3(GT), 0, st, op, qfac, wtab, tab_count,
-                         g0, dg, u, mu, nrhs, (unsigned)first, g);
+  auto launch = [&](auto kernel, int gx, int gy, int gz) {
+    const long long tiles = (long long)((op.nx + gx - 1) / gx) * ((op.ny + gy - 1) / gy) *
+                            ((op.nz + gz - 1) / gz);
+    // A launch holds fewer than 2^32 threads, which badly filled tiles can exceed
+    // (5 x 3 x 2^26 nodes, half of what a grid may have, take 2^24 tiles and
+    // more): 2^20 tiles, over a millisecond's work, per launch.
+    constexpr long long MAX_TILES = 1LL << 20;
+    for (long long first = 0; first < tiles; first += MAX_TILES)
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(MAX_TILES, tiles - first)), dim3(GT), 0,
+                         st, op, qfac, wtab, tab_count, g0, dg, u, mu, nrhs, (unsigned)first, g);
+  };
+  // Rows of 16 nodes are what the loads want; with a few nodes along x most of a
+  // tile is empty, and one right-hand side took longer than without tiles (400 x
+  // 400 x 3 nodes 222 us against 157).
+  if (op.nx <= 8) {
+    if (weights) launch(gradient_kernel<true, 4, 8, 8>, 4, 8, 8);
+    else launch(gradient_kernel<false, 4, 8, 8>, 4, 8, 8);
+  } else {
+    if (weights) launch(gradient_kernel<true, 16, 4, 4>, 16, 4, 4);
+    else launch(gradient_kernel<false, 16, 4, 4>, 16, 4, 4);
   }
 }
 

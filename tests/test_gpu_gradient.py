@@ -28,10 +28,17 @@ def test_gradient_tiles(n, nrhs):
         assert np.abs(g - ref).max() < 1e-11 * np.abs(ref).max()
 
 
+# tiles of 4 x 8 x 8 nodes up to 8 nodes along x, at their edges
+@pytest.mark.parametrize("n", [(4, 8, 8), (5, 9, 7), (8, 17, 9), (9, 8, 8)])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_gradient_tiles_of_narrow_grids(n, nrhs):
+    test_gradient_tiles(n, nrhs)
+
+
 def test_gradient_of_more_tiles_than_a_launch_holds():
-    """A grid of few nodes along two axes has 2^24 tiles, 2^32 threads, in half
-    a billion nodes.  Its fields repeat along z, so away from the ends its
-    gradient repeats that of a short grid, tile by tile."""
+    """Half a billion nodes, few of them along two axes, whose tiles may need
+    2^32 threads.  The fields repeat along z, so away from the ends the gradient
+    repeats that of a short grid, tile by tile."""
     need_gpu()
     import torch
     if torch.cuda.mem_get_info()[0] < 150e9:
