@@ -132,3 +132,31 @@ def test_fp32_apply_does_not_depend_on_the_block(nrhs):
     x = to_dev(rand_field((w.nz, w.ny, w.nx), 64, 66), S)
     big = S.apply_A(x, prec=1)
     assert bool((S.apply_A(x[:nrhs].contiguous(), prec=1) == big[:nrhs]).all())
+
+
+# y in the place of x, a part of a field above it and a part of a field below
+# it; the grids and columns of every tile height
+@pytest.mark.parametrize("n,nrhs", [((33, 34, 3), 1), ((33, 34, 41), 17), ((41, 42, 37), 33)])
+@pytest.mark.parametrize("prec", [1, 2])
+def test_apply_of_overlapping_arrays(n, nrhs, prec):
+    """Through the C ABI, which alone takes overlapping arrays: x is read in
+    full before y is written, with the values of separate arrays bit for bit."""
+    need_gpu()
+    import torch
+    from paper_2110_15113_amd import oras
+    w = wl.small_random(n, npml=1, q=70.0, seed=67)
+    S = setup(w, prec=1)
+    x = to_dev(rand_field((w.nz, w.ny, w.nx), nrhs, 68), S)
+    ref = S.apply_A(x, prec=prec)
+    count, part = x.numel(), x[0].numel() // 2 + 1
+    calls = [oras.lib().oras_apply_A]
+    if count * 48 < oras.lib().oras_noalloc_scratch_bytes():
+        calls.append(oras.lib().oras_apply_A_noalloc)
+    for call in calls:
+        for shift in (0, part, -part):
+            buf = torch.full((count + 2 * part,), float("nan"), dtype=torch.complex128,
+                             device=S.device)
+            xs, ys = buf[part:part + count], buf[part + shift:part + shift + count]
+            xs.copy_(x.view(-1))
+            S._check(call(S._ctx, oras._ptr(xs), oras._ptr(ys), nrhs, prec))
+            assert torch.equal(ys, ref.view(-1)), (call.__name__, shift)
