@@ -61,7 +61,7 @@ extern "C" oras_status oras_apply_A_noalloc(oras_ctx c, const void* x_dev, void*
     return oras::set_error(c, ORAS_E_ARG, msg.c_str());
   }
   oras_status direct = ORAS_OK;
-  if (!oras::apply_A_in_place(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
+  if (oras::apply_A_direct(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
   const int dev = oras::ctx_device(c);
   void* base = nullptr;
   {

@@ -596,11 +596,11 @@ oras_status apply_A_staged(oras_ctx c, const void* x_dev, void* y_dev, int nrhs,
 
 // The caller's layout is read and written by the apply itself, unless the two
 // arrays overlap: then x has to be read in full first.
-bool apply_A_in_place(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
-                      oras_status* st) {
+bool apply_A_direct(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
+                    oras_status* st) {
   const size_t bytes = (size_t)c->n * nrhs * sizeof(double2);
   const uintptr_t x = (uintptr_t)x_dev, y = (uintptr_t)y_dev;
-  if (x < y + bytes && y < x + bytes) return true;
+  if (x < y + bytes && y < x + bytes) return false;
   *st = [&]() -> oras_status {
     if (prec == ORAS_C64)
       launch_stencil_mf_planar<float>(mf_view<float>(c), (const double2*)x_dev, (double2*)y_dev,
@@ -612,7 +612,7 @@ bool apply_A_in_place(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int 
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return ORAS_OK;
   }();
-  return false;
+  return true;
 }
 
 oras_status set_error(oras_ctx c, oras_status st, const char* msg) { return fail(c, st, msg); }
@@ -1382,7 +1382,7 @@ oras_status oras_subdomain(oras_ctx c, int j, int* nsub, int* box12) {
 oras_status oras_apply_A(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec) {
   TRY(oras::check_apply_A(c, x_dev, y_dev, nrhs, prec));
   oras_status direct = ORAS_OK;
-  if (!oras::apply_A_in_place(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
+  if (oras::apply_A_direct(c, x_dev, y_dev, nrhs, prec, &direct)) return direct;
   const long long s = pad_s(nrhs);
   TRY(dev_alloc(c, c->Bint, (size_t)(c->n * s) * sizeof(double2)));
   TRY(dev_alloc(c, c->Tmp, (size_t)(c->n * s) * sizeof(double2)));

@@ -351,10 +351,10 @@ oras_status check_apply_A(oras_ctx c, const void* x_dev, const void* y_dev, int 
 size_t apply_A_scratch_bytes(oras_ctx c, int nrhs, int prec);
 oras_status apply_A_staged(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
                            double2* xin, double2* yout, float2* x32);
-// false: x and y do not overlap and y = A x was formed straight from the
-// caller's arrays, with the result in *st
-bool apply_A_in_place(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
-                      oras_status* st);
+// true: x and y do not overlap and y = A x was formed straight from the
+// caller's arrays, with the result in *st; false: they overlap, nothing was done
+bool apply_A_direct(oras_ctx c, const void* x_dev, void* y_dev, int nrhs, int prec,
+                    oras_status* st);
 oras_status set_error(oras_ctx c, oras_status st, const char* msg);
 int ctx_device(oras_ctx c);
 // Records the address of `device`'s copy of the no-alloc scratch array
