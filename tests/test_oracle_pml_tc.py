@@ -110,3 +110,22 @@ def test_fgmres_with_pml_interfaces_reaches_the_direct_solution():
         err = np.linalg.norm(x - x_ref.reshape(-1)) / np.linalg.norm(x_ref)
         assert err < 1e-7, (ov, err)
         assert it < 60, (ov, it)
+
+
+@pytest.mark.parametrize("interface,ov", [("robin", 0), ("robin", 1), ("pml", 1), ("pml", 2)])
+@pytest.mark.parametrize("npml,q,free_surface,other_m", [(0, None, False, False), (1, 40.0, True, True),
+                                                         (2, 40.0, False, True), (2, None, True, False)])
+def test_every_local_matrix_is_complex_symmetric(interface, ov, npml, q, free_surface, other_m):
+    """The factorisation keeps one triangle of each plane: it rests on B = B^T
+    for every interface, overlap, absorbing layer, free surface, attenuation and
+    squared slowness, weights frozen at another model included."""
+    rng = np.random.default_rng(12)
+    for n in ((9, 8, 7), (5, 9, 6), (12, 6, 5)):
+        w = wl.small_random(n, npml=npml, q=q, seed=3)
+        m = (1 / w.vel ** 2) * (1 + 0.5 * rng.random(w.vel.shape)) if other_m else None
+        F = op.make_fields(w.vel, w.Q, w.omega, w.h, w.npml, m=m, free_surface=free_surface)
+        for parts in ((2, 2, 1), (1, 2, 2)):
+            M = oras.ORAS(F, parts, ov, interface=interface)
+            for j in range(len(M.subs)):
+                B = M.local_matrix(j)
+                assert abs(B - B.T).max() == 0.0
