@@ -294,8 +294,12 @@ oras_status oras_blr_ranks(oras_ctx ctx, int sub, int plane, int* ranks_host, in
  * oras_apply_M: y = M^{-1} x = sum_j R_j^T D_j B_j^{-1} R_j x, the one-level
  *   ORAS preconditioner of sec. 2.1 with the local solves of sec. 2.2, with
  *   the current factors.
- * x, y: (nrhs, nz, ny, nx) complex128, 1 <= nrhs <= 256, device, caller-owned.
- * Internal staging buffers are allocated by the context and kept. */
+ * x, y: (nrhs, nz, ny, nx) complex128, 1 <= nrhs <= 256, device, caller-owned;
+ *   x and y may overlap (x is then read in full before y is written).
+ * Internal staging buffers are allocated by the context and kept.
+ * Equal calls give equal bits.  A column's result may differ at rounding level
+ * between blocks of different widths, in which tiles and the order of sums follow
+ * the number of columns. */
 oras_status oras_apply_A(oras_ctx ctx, const void* x_dev, void* y_dev, int nrhs, int prec);
 oras_status oras_apply_M(oras_ctx ctx, const void* x_dev, void* y_dev, int nrhs);
 

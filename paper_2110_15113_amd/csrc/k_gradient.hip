@@ -16,13 +16,15 @@
 // Both need, per node, the 27 sums over the right-hand sides of the products
 // of u and mu with their neighbours, and nothing else of u and mu.  A
 // work-group owns a 16 x 4 x 4 tile of nodes (4 x 8 x 8 where the grid has few
-// along x), keeps its 27 sums in registers and streams the right-hand sides through LDS (tile and halo, two buffers,
-// the next one's loads in flight), so u and mu are read once from memory and
-// the halo's share (2.5 times the tile) again from the caches.  Bound by the
-// 53 complex multiply-adds per node and right-hand side on the FP64 vector
-// unit: 96^3 nodes, 32 right-hand sides take 0.58 ms (14.1 ms with one
-// thread per node gathering every product from memory, a pass for each of the
-// two parts and seven for the stiffness weights).
+// along x), keeps its 27 sums in registers and streams the right-hand sides
+// through LDS (tile and halo, two buffers, the next one's loads in flight), so u
+// and mu are read once from memory and the halo's share (1.5 times the tile)
+// again from the caches.  Bound by its LDS reads, 54 of 16 bytes per node and
+// right-hand side: 0.31 of the 0.58 ms that 96^3 nodes with 32 right-hand sides
+// take, at 128 bytes per CU and clock (its 53 complex multiply-adds are 0.15 ms
+// of the FP64 vector unit; 14.1 ms with one thread per node gathering every
+// product from memory, a pass for each of the two parts and seven for the
+// stiffness weights).
 #include <algorithm>
 
 #include "oras_internal.h"
