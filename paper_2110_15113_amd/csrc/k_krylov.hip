@@ -14,11 +14,29 @@ namespace oras {
 
 namespace {
 
+// [nrhs][n] -> [n][s], one 16-byte value per lane: up to 16 columns a node's
+// values are at most two cache lines, and what a wave reads of each column is a
+// run of 64 bytes or more (160^3 nodes, 1, 8 and 16 columns: 113, 172 and 406 us;
+// 175, 233 and 390 through the LDS tile below, which is then half empty or more).
+__global__ void to_internal_direct_kernel(const double2* __restrict__ src,
+                                          double2* __restrict__ dst, long long n, int nrhs, int s,
+                                          int conj) {
+  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= n * s) return;
+  const long long node = idx / s;
+  const int c = (int)(idx % s);
+  double2 v = make_double2(0.0, 0.0);
+  if (c < nrhs) {
+    v = src[(long long)c * n + node];
+    if (conj) v.y = -v.y;
+  }
+  dst[idx] = v;
+}
+
 // [nrhs][n] <-> [n][s] through an LDS tile of 64 nodes x 32 columns, so that
 // both the reads and the writes (a node's columns, a column's nodes) are
-// contiguous runs (160^3 nodes, 32 columns inwards: 791 us; with one 16-byte
-// value per lane read at a stride of n 916, and 3540 for 64 columns of 192 x
-// 192 x 96 nodes).
+// contiguous runs (160^3 nodes, inwards: 24 columns 575 us and 32 773, with one
+// value per lane 592 and 925; 64 columns of 192 x 192 x 96 nodes 3540 that way).
 constexpr int TR_NODES = 64, TR_COLS = 32;
 __global__ void __launch_bounds__(256)
 to_internal_kernel(const double2* __restrict__ src, double2* __restrict__ dst, long long n,
@@ -453,6 +471,11 @@ inline int group_threads(int s) {
 
 void launch_to_internal(const double2* src, double2* dst, long long n, int nrhs, int s, int conj,
                         hipStream_t st) {
+  if (s <= 16 && n * s < (1LL << 32) - 256) {      // a thread per value in one launch
+    hipLaunchKernelGGL(to_internal_direct_kernel, dim3(blocks_for(n * s, 256)), dim3(256), 0, st,
+                       src, dst, n, nrhs, s, conj);
+    return;
+  }
   const dim3 grid((unsigned)((n + TR_NODES - 1) / TR_NODES),
                   (unsigned)((s + TR_COLS - 1) / TR_COLS));
   hipLaunchKernelGGL(to_internal_kernel, grid, dim3(256), 0, st, src, dst, n, nrhs, s, conj);
