@@ -483,11 +483,11 @@ template <int NT> __device__ inline double2 buf_ld(BufRsrc r, int vo, int so) {
 // from s on (a block of 32 over the last 24) read the following row's values
 // and are not stored.
 //
-// What bounds it at 32 columns: with every operand taken from L1 the same
-// kernel runs at 62 TFLOP/s on 320 subdomains of 576-node planes (the rest of
-// the 77 TFLOP/s a large matrix product reaches is ramp, tail and the sums),
-// with the factors streamed from HBM at 51; at 16 and 8 columns the stream,
-// 4.7 - 5.1 TB/s of 5.1 for a large copy.
+// What bounds it at 32 columns: with every operand taken from L1 the 16-row,
+// four-wave form runs at 62 TFLOP/s on 320 subdomains of 576-node planes (the
+// rest of the 77 TFLOP/s a large matrix product reaches is ramp, tail and the
+// sums), with the factors streamed from HBM at 52, 32 rows at 53 (64 columns: 56);
+// at 16 and 8 columns the stream, 4.7 - 5.1 TB/s of 5.1 for a large copy.
 template <int NC, int RS, int KS, int PF>
 __global__ void __launch_bounds__(64 * KS)
 plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, int ncg, int k,
@@ -646,7 +646,8 @@ plane_gemm_f64_kernel(const SubDesc* __restrict__ subs, int nsub, int max_rg, in
 //   * 32 rows, 4 waves in large launches, whose row halves share the t operand:
 //     128^3 in 512 boxes of 256 / 324 / 400 nodes a plane 175 / 277 / 366 (186 /
 //     319 / 413), with 64 columns 324 / 526 / 696 (331 / 530 / 699), 120^3 in 216
-//     290 (340); 16 rows 197 / 297 / 389, 371 / 592 / 767 and 299.
+//     290 (340), 160 x 160 x 100 in 320 441 (492), 64 columns 832 (870); 16 rows
+//     197 / 297 / 389, 371 / 592 / 767, 299, 442 and 872.
 //   * 16 rows, 4 waves below: 96^3 in 64 163 (227), 61 x 47 x 53 in 18 28 (60),
 //     32^3 in 8 13 (42); 32 rows 172, 32 and 19.
 //   * Short planes give fewer waves enough k-steps: 2 waves up to 6 row tiles
