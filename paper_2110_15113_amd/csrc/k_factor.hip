@@ -294,7 +294,8 @@ template <int N, typename F> __device__ inline void static_for(F&& f) {
   static_for_impl(std::make_integer_sequence<int, N>(), f);
 }
 
-// A <- A^{-1} of a 16 x 16 block at m (row stride ld) by one wave: unblocked
+// A <- A^{-1} of a symmetric 16 x 16 block at m (row stride ld), its upper
+// triangle being read, by one wave: unblocked
 // Gauss-Jordan in registers, lane (r = l % 16, g = l / 16) holding row r,
 // columns 4 g .. 4 g + 3; the pivot row comes by DPP, the pivot column by lane
 // swaps, the pivot by a lane read, so no pivot step waits at a barrier or for
@@ -307,7 +308,7 @@ __device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& ba
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   T a[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = m[r * ld + 4 * g + j];
+  for (int j = 0; j < 4; ++j) a[j] = m[min(r, 4 * g + j) * ld + max(r, 4 * g + j)];
   static_for<16>([&](auto P) {
     constexpr int piv = decltype(P)::value, pg = piv / 4, pj = piv % 4;
     T p;
@@ -395,7 +396,13 @@ __device__ inline void block_product(Block<R> D, Block<R> X, Block<R> Y, C<R>* m
 // inverts the next diagonal block in registers, ahead of the other waves in
 // instruction priority, while those finish the step, and the products run on
 // the matrix unit.  The matrix stays symmetric but for the sign between
-// eliminated and other blocks, so of A_ij and A_ji one is computed.
+// eliminated and other blocks, so of A_ij and A_ji one is computed.  Of a
+// diagonal block only the upper triangle enters its inverse: block row and
+// column then belong to the same matrix.  With both triangles, equal but for
+// rounding, the inverse is not symmetric, the column (the transposed row) that
+// of another matrix, and near a small pivot p the difference, eps / p^2, stays in
+// the result (FP32, boxes of 11 x 35 x 3 nodes with pivots down to 1e-3 of the
+// largest entry: error of a local solve up to 2.3e-3, 7e-5 with one triangle).
 //
 // 64 complex FP64 rows 28 us a call: 64 pivots of 0.27 (about 25 dependent FP64
 // instructions each), the rest are products, loads and stores; 33 with the next
@@ -433,9 +440,9 @@ gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
     const int i = n * NTHR + threadIdx.x, t = i / TT, e = i % TT;
     const int tj = (t > 0) + (t > 2) + (t > 5), ti = t - tj * (tj + 1) / 2;
     const int row = ti * TILE + ((e >> 2) & 31), col = tj * TILE + (e >> 7) * 4 + (e & 3);
-    if (tj >= nb) continue;
+    if (tj >= nb || row > col) continue;
     A[row * LD + col] = v[n];
-    if (ti < tj) A[col * LD + row] = v[n];
+    A[col * LD + row] = v[n];
   }
   __syncthreads();
   R mag_min = INFINITY;    // smallest |pivot|^2 seen (wave 0)

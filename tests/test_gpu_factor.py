@@ -7,8 +7,8 @@ import pytest
 from oracle import oras as ooras
 from paper_2110_15113_amd import workloads as wl
 
-from gpu_util import (FP32_BOX, FP64_BOX, box_err, need_gpu, oracle_fields, rand_field, say, setup,
-                      to_dev)
+from gpu_util import (EPS32, FP32_BOX, FP64_BOX, box_err, need_gpu, oracle_fields, rand_field,
+                      say, setup, to_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,33 @@ def test_factor_memory(n, parts, prec):
     say(f"factor memory {n} {parts} prec {prec}: {used} of {nsub * sub * entry}")
     # descriptors and statistics: well below 1 KB a subdomain, 2 MB pages
     assert used <= nsub * (sub * entry + 1024) + (16 << 20)
+
+
+@pytest.mark.parametrize("n,parts,ov", [((11, 58, 3), (5, 3, 1), 8), ((3, 203, 11), (1, 1, 1), 2)])
+def test_factor_near_small_pivots(n, parts, ov):
+    """Thin boxes of forty rough models, whose pivots go down to r = 1e-3 of
+    their plane's largest entry.  Elimination without row exchanges makes backward
+    errors of eps / r, in each of the 2 s_z plane products of a local solve;
+    block rows and columns that belong to different matrices (a diagonal block's
+    inverse that is not symmetric) leave eps / r^2."""
+    need_gpu()
+    import torch
+    from oracle import operator as op
+    from paper_2110_15113_amd import oras
+    nx, ny, nz = n
+    omega, h = 2 * np.pi * 6.0, 20.0
+    x = rand_field((nz, ny, nx), 1, 90)
+    S = oras.Solver(0)
+    worst = 0.0
+    for seed in range(40):
+        g = torch.Generator().manual_seed(seed)
+        vel = 1500 + 3000 * torch.rand((nz, ny, nx), generator=g, dtype=torch.float64)
+        ref = ooras.ORAS(op.make_fields(vel.numpy(), None, omega, h, 1), parts, ov).apply(x)
+        S.assemble(vel.to(S.device), h, 1, omega, prec=1)
+        S.factor(parts, ov, 1)
+        r = S.factor_stats()[0]
+        y = S.apply_M(to_dev(x, S)).cpu().numpy()
+        e = float(np.linalg.norm(y - ref) / np.linalg.norm(ref))
+        worst = max(worst, e * r / (2 * nz * EPS32))
+        assert e < 2 * nz * EPS32 / r, (seed, r, e)
+    say(f"small pivots {n}: at most {worst:.2f} of the bar")
