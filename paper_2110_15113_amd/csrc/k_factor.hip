@@ -294,18 +294,21 @@ template <int N, typename F> __device__ inline void static_for(F&& f) {
   static_for_impl(std::make_integer_sequence<int, N>(), f);
 }
 
-// A <- A^{-1} of a symmetric 16 x 16 block at m (row stride ld), its upper
-// triangle being read, by one wave: unblocked
-// Gauss-Jordan in registers, lane (r = l % 16, g = l / 16) holding row r,
-// columns 4 g .. 4 g + 3; the pivot row comes by DPP, the pivot column by lane
-// swaps, the pivot by a lane read, so no pivot step waits at a barrier or for
-// LDS.  The pivot row itself is 0 - (-1 / p) times the old one, which makes it
-// a row like the others.  The smallest |pivot|^2 of the first `count` pivots
-// goes to mag_min, a zero or non-finite one to bad.
+// A = L D L^T of a symmetric 16 x 16 block at m (row stride ld; its upper triangle
+// is read) by one wave: W = L^{-1} to w (row stride 17) and D^{-1} to d.
+// Unblocked elimination in registers, lane (r = l % 16, g = l / 16) holding row
+// r, columns 4 g .. 4 g + 3, of what is left of A right of the pivot and of W left
+// of it; the pivot row comes by DPP, the pivot column by lane swaps, the pivot by
+// a lane read, so no pivot step waits at a barrier or for LDS.  The smallest
+// |pivot|^2 of the first `count` pivots goes to mag_min, a zero or non-finite one
+// to bad.
 template <typename R>
-__device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& bad) {
+__device__ inline void factor16(const C<R>* m, int ld, C<R>* w, C<R>* d, int count, R& mag_min,
+                                bool& bad) {
   using T = C<R>;
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));   // its comparisons are not kept from call to call (spills)
+  const int r = lane & 15, g = lane >> 4;
   T a[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) a[j] = m[min(r, 4 * g + j) * ld + max(r, 4 * g + j)];
@@ -321,70 +324,98 @@ __device__ inline void invert16(C<R>* m, int ld, int count, R& mag_min, bool& ba
     for (int j = 0; j < 4; ++j) {
       rv[j].x = row_bcast<piv>(a[j].x);
       rv[j].y = row_bcast<piv>(a[j].y);
-      a[j].x = r == piv ? (R)0 : a[j].x;
-      a[j].y = r == piv ? (R)0 : a[j].y;
     }
     const R mag = p.x * p.x + p.y * p.y;
     const bool ok = isfinite(p.x) & isfinite(p.y) & (mag > Tiny<R>::v);
     bad |= !ok;
     mag_min = ok & (piv < count) & (mag < mag_min) ? mag : mag_min;
     const R inv = (R)1 / mag;
-    T f;                                             // A_r,piv / p, or -1 / p
-    f.x = (r == piv ? -p.x : cv.x * p.x + cv.y * p.y) * inv;
-    f.y = (r == piv ? p.y : cv.y * p.x - cv.x * p.y) * inv;
+    T f;                                             // A_r,piv / p below the pivot, else 0
+    f.x = r > piv ? (cv.x * p.x + cv.y * p.y) * inv : (R)0;
+    f.y = r > piv ? (cv.y * p.x - cv.x * p.y) * inv : (R)0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) cfms(a[j], f, rv[j]);
-    if (g == pg) {                                   // -A_r,piv / p, 1 / p
+    if (g == pg && r > piv) {                        // W_r,piv
       a[pj].x = -f.x;
       a[pj].y = -f.y;
     }
   });
 #pragma unroll
-  for (int j = 0; j < 4; ++j) m[r * ld + 4 * g + j] = a[j];
+  for (int j = 0; j < 4; ++j) {
+    const int c = 4 * g + j;
+    w[r * 17 + c] = c < r ? a[j] : (c == r ? cone<T>() : czero<T>());
+    if (c == r) {                                    // the pivot
+      const R inv = (R)1 / (a[j].x * a[j].x + a[j].y * a[j].y);
+      d[r].x = a[j].x * inv;
+      d[r].y = -a[j].y * inv;
+    }
+  }
 }
 
-// One wave's 16 x 16 block: D <- D - X Y (SUB) or X Y, blocks
-// in LDS; YT: minus the transposed block at Y for Y.  Every operand is read
-// before D is written, so D may be any of them.  The result also goes to
-// `mirror` if that is not null, transposed and times sign.
+// Products of one wave's 16 x 16 blocks in LDS.  Every operand is read before a
+// result is written, so the result may take the place of any of them.
 template <typename R> struct Block {
   C<R>* p;
   int ld;        // row stride
   __device__ C<R>& operator()(int r, int c) const { return p[r * ld + c]; }
 };
-template <typename R, bool SUB, bool YT>
-__device__ inline void block_product(Block<R> D, Block<R> X, Block<R> Y, C<R>* mirror = nullptr,
-                                     R sign = 1) {
-  using T = C<R>;
+// acc += sign X Y
+template <typename R, typename FX, typename FY>
+__device__ inline void block_mac(typename Mma16<R>::V& re, typename Mma16<R>::V& im, R sign, FX X,
+                                 FY Y) {
   using M = Mma16<R>;
-  const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
-  typename M::V re, im;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    T d = czero<T>();
-    if (SUB) d = D(M::row(kk, i), m);
-    re[i] = d.x;
-    im[i] = d.y;
-  }
+  const int m = threadIdx.x & 15, kk = (threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const T x = X(m, 4 * q + kk), y = YT ? Y(m, 4 * q + kk) : Y(4 * q + kk, m);
-    const R xr = SUB || YT ? -x.x : x.x, xi = SUB || YT ? -x.y : x.y;
+    const C<R> x = X(m, 4 * q + kk), y = Y(4 * q + kk, m);
+    const R xr = sign * x.x, xi = sign * x.y;
     re = M::mac(xr, y.x, re);
     im = M::mac(xr, y.y, im);
     re = M::mac(-xi, y.y, re);
     im = M::mac(xi, y.x, im);
   }
+}
+// A <- W A
+template <typename R> __device__ inline void block_w(Block<R> A, Block<R> W) {
+  using M = Mma16<R>;
+  const int m = threadIdx.x & 15, kk = (threadIdx.x & 63) >> 4;
+  typename M::V re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+  block_mac<R>(re, im, (R)1, W, A);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    T d;
-    d.x = re[i];
-    d.y = im[i];
-    D(M::row(kk, i), m) = d;
+    C<R> v;
+    v.x = re[i];
+    v.y = im[i];
+    A(M::row(kk, i), m) = v;
+  }
+}
+// A <- A + sign X^T D Y with D diagonal (SUM; its transpose times msign also to
+// mirror if that is not null), or (X^T D Y)^T times msign to mirror.
+template <typename R, bool SUM>
+__device__ inline void block_tdy(Block<R> A, R sign, Block<R> X, const C<R>* d, Block<R> Y,
+                                 C<R>* mirror, R msign) {
+  using T = C<R>;
+  using M = Mma16<R>;
+  const int m = threadIdx.x & 15, kk = (threadIdx.x & 63) >> 4;
+  typename M::V re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+  if (SUM) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      re[i] = A(M::row(kk, i), m).x;
+      im[i] = A(M::row(kk, i), m).y;
+    }
+  }
+  block_mac<R>(re, im, sign, [&](int row, int k) { return cmul(X(k, row), d[k]); }, Y);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    T v;
+    v.x = re[i];
+    v.y = im[i];
+    if (SUM) A(M::row(kk, i), m) = v;
     if (mirror) {
-      d.x *= sign;
-      d.y *= sign;
-      mirror[m * D.ld + M::row(kk, i)] = d;
+      v.x *= msign;
+      v.y *= msign;
+      mirror[m * A.ld + M::row(kk, i)] = v;
     }
   }
 }
@@ -393,23 +424,29 @@ __device__ inline void block_product(Block<R> D, Block<R> X, Block<R> Y, C<R>* m
 // Gauss-Jordan over 16 x 16 blocks of the matrix in LDS, one work-group per
 // subdomain.  It is a chain (few work-groups, every other kernel of the plane
 // waits for it), so what counts is the length of a step: wave 0 updates and
-// inverts the next diagonal block in registers, ahead of the other waves in
+// factors the next diagonal block in registers, ahead of the other waves in
 // instruction priority, while those finish the step, and the products run on
 // the matrix unit.  The matrix stays symmetric but for the sign between
-// eliminated and other blocks, so of A_ij and A_ji one is computed.  Of a
-// diagonal block only the upper triangle enters its inverse: block row and
-// column then belong to the same matrix.  With both triangles, equal but for
-// rounding, the inverse is not symmetric, the column (the transposed row) that
-// of another matrix, and near a small pivot p the difference, eps / p^2, stays in
-// the result (FP32, boxes of 11 x 35 x 3 nodes with pivots down to 1e-3 of the
-// largest entry: error of a local solve up to 2.3e-3, 7e-5 with one triangle).
+// eliminated and other blocks, so of A_ij and A_ji one is computed.
+//
+// A diagonal block enters as L D L^T, not as its inverse: with W = L^{-1} and
+// Y_j = W A_bj the update is A_ij -= +- Y_i^T D^{-1} Y_j and the block row W^T
+// D^{-1} Y_j.  Where a block is a large multiple s of a rank-one matrix plus a
+// rest (the plane before it was nearly singular), products with its inverse
+// leave eps s^2 in the result, those with L and D eps s, as elimination row by
+// row does (complex64 solve of a box of 18 x 23 x 37 nodes: error 4.7e-3, 3.6e-5
+// and 5.4e-5).  Only the upper triangle of a diagonal block is read: with both,
+// equal but for rounding, block row and column would belong to different
+// matrices, which near a small pivot p leaves eps / p^2 (boxes of 11 x 35 x 3
+// nodes: up to 2.3e-3, 7e-5 with one).
 //
 // 64 complex FP64 rows 28 us a call: 64 pivots of 0.27 (about 25 dependent FP64
-// instructions each), the rest are products, loads and stores; 33 with the next
-// inverse after the update and both halves computed, 75 for 64 pivot steps with
-// two barriers each.  128 complex FP32 rows on 256 subdomains, beside the other
-// 256's products, 86 us against 131 and 305.  A factorisation of 32^3 in 8 subdomains, which little
-// else but this chain keeps waiting, 6.7 ms in FP64 and 4.2 in FP32 (7.2, 5.4).
+// instructions each), the rest are products, loads and stores; as much with
+// explicit inverses, 75 for 64 pivot steps with two barriers each.  128 complex
+// FP32 rows on 64 subdomains, beside other kernels, 51 us (48 with inverses).  A
+// factorisation of 32^3 in 8 subdomains, which little else but this chain keeps
+// waiting, 6.4 ms in FP64 and 4.2 in FP32 (6.4, 4.1 with inverses).
+//
 // stats[2 (sub max_sz + k) + 1] receives the bits of max 1 / |pivot|^2.
 template <typename R>
 __global__ void __launch_bounds__(64 * GjBlock<R>::WAVES)
@@ -418,6 +455,7 @@ gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
   using T = C<R>;
   constexpr int NB = TILE * GjBlock<R>::NBT, LD = NB + 1, WAVES = GjBlock<R>::WAVES;
   __shared__ __align__(16) T A[NB * LD];      // 132 KB FP32, 65 KB FP64
+  __shared__ __align__(16) T wbuf[2][16 * 17], dbuf[2][16];   // W and D^{-1} of a diagonal block
   const SubDesc sd = subs[blockIdx.x];
   if (k >= sd.sz || kb0 >= sd.nt) return;
   const int nb = min(GjBlock<R>::NBT, sd.nt - kb0);
@@ -448,49 +486,57 @@ gj_diag_kernel(const SubDesc* subs, int k, int kb0, C<R>* fac, int* status,
   R mag_min = INFINITY;    // smallest |pivot|^2 seen (wave 0)
   bool bad = false;
   const int live = sd.p - TILE * kb0;     // pivots that are not padding
+  // Between steps, block row b - 1 holds the Y_j of its step and block column
+  // b - 1 the values of both.
   for (int b = -1; b < nblk; ++b) {
-    // block row b <- A_bb^{-1} A_bj; column b - 1 is not written yet, it is
-    // minus the transposed row b - 1 here
-    for (int j = wv; j < nblk && b >= 0; j += WAVES) {
-      if (j == b) continue;
-      if (j == b - 1) block_product<R, false, true>(at(b, j), at(b, b), at(j, b));
-      else block_product<R, false, false>(at(b, j), at(b, b), at(b, j));
-    }
+    const Block<R> W{wbuf[b & 1], 17};
+    const T* d = dbuf[b & 1];
+    // block row b <- Y_j = W A_bj
+    for (int j = wv; j < nblk && b >= 0; j += WAVES)
+      if (j != b) block_w<R>(at(b, j), W);
     __syncthreads();
-    // wave 0: the next diagonal block and its inverse; the rest: the other
-    // blocks of the update, one of (i, j) and (j, i) each, for b - 1 the one in
-    // row b - 1.  Column b keeps its old values, which the update reads.
+    // wave 0: the next diagonal block and its factors; the rest: the other blocks
+    // of the update, one of (i, j) and (j, i) each, for b - 1 the one in column
+    // b - 1, then block column b, the transposed row W^T D^{-1} Y_j, and the
+    // inverse of the diagonal block
     const bool ahead = b + 1 < nblk;
     if (ahead && wv == 0) {
       __builtin_amdgcn_s_setprio(3);
       if (b >= 0)
-        block_product<R, true, false>(at(b + 1, b + 1), at(b + 1, b), at(b, b + 1));
+        block_tdy<R, true>(at(b + 1, b + 1), (R)-1, at(b, b + 1), d, at(b, b + 1), nullptr, (R)1);
       wave_lds_sync();
-      invert16<R>(at(b + 1, b + 1).p, LD, live - 16 * (b + 1), mag_min, bad);
+      factor16<R>(at(b + 1, b + 1).p, LD, wbuf[(b + 1) & 1], dbuf[(b + 1) & 1],
+                  live - 16 * (b + 1), mag_min, bad);
       __builtin_amdgcn_s_setprio(0);
     } else if (b >= 0) {
       const int first = ahead ? wv - 1 : wv, step = ahead ? WAVES - 1 : WAVES;
-      for (int t = first; t < nblk * (nblk - 1) / 2; t += step) {
+      const int pairs = nblk * (nblk - 1) / 2;
+      for (int t = first; t < pairs + nblk; t += step) {
+        if (t >= pairs) {
+          const int j = t - pairs;
+          block_tdy<R, false>(at(j, b), (R)1, W, d, j == b ? W : at(b, j), at(j, b).p,
+                              j <= b ? (R)1 : (R)-1);
+          continue;
+        }
         int j = 0;
         while ((j + 1) * (j + 2) / 2 <= t) ++j;
         int i = t - j * (j + 1) / 2;       // i <= j of the nblk - 1 blocks but b
         i += i >= b;
         j += j >= b;
         if (ahead && i == b + 1 && j == b + 1) continue;
-        if (j == b - 1) {
-          j = i;
-          i = b - 1;
+        if (i == b - 1) {
+          i = j;
+          j = b - 1;
         }
-        block_product<R, true, false>(at(i, j), at(i, b), at(b, j),
-                                      i == j ? nullptr : at(j, i).p,
-                                      (i <= b) == (j <= b) ? (R)1 : (R)-1);
+        block_tdy<R, true>(at(i, j), i < b ? (R)1 : (R)-1, at(b, i), d, at(b, j),
+                           i == j ? nullptr : at(j, i).p, (i <= b) == (j <= b) ? (R)1 : (R)-1);
       }
     }
     __syncthreads();
   }
-  // the last block column: the transposed last row
+  // the last block row: the transposed last column
   for (int i = threadIdx.x; i < (nblk - 1) * 256; i += 64 * WAVES)
-    at(i >> 8, nblk - 1)((i >> 4) & 15, i & 15) = at(nblk - 1, i >> 8)(i & 15, (i >> 4) & 15);
+    at(nblk - 1, i >> 8)(i & 15, (i >> 4) & 15) = at(i >> 8, nblk - 1)((i >> 4) & 15, i & 15);
   __syncthreads();
   for (int i = threadIdx.x; i < nb * nb * TILE * TILE; i += 64 * WAVES) {
     const int t = i / (TILE * TILE), e = i % (TILE * TILE);
