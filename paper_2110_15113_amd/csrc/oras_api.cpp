@@ -380,8 +380,12 @@ void apply_stencil(oras_ctx c, const C<R>* x, const double2* b, Y* y, int s, hip
 // 256 nodes left 32^3 nodes with 8 columns 128 work-groups of eight iterations:
 // with a mean of 7 basis vectors the product and update passes took 29.8 and
 // 27.8 us, now 12.8 and 8.0; 61 x 47 x 53 nodes 59.5 and 58.2, now 53.3 and 41.9.)
+// Each keeps a partial sum per column and basis vector, so one per 8 nodes at
+// most: an eighth of the basis (small grids with more than 32 columns; up to
+// the size of the basis without this.  Solves of 256 columns, 30 iterations, without
+// and with it: 16^3 nodes 16.7 and 13.6 ms, 12^3 12.6 and 10.7, 8^3 6.9 and 8.5).
 int nblk_for(long long n, long long s) {
-  return (int)std::max(1LL, std::min(2048LL, (n * s + 255) / 256));
+  return (int)std::max(1LL, std::min({2048LL, (n * s + 255) / 256, (n + 7) / 8}));
 }
 
 // y (internal [n][s] c128) = A x in precision prec; x internal c128.

@@ -163,3 +163,23 @@ def test_krylov_and_basis_precisions():
     r0 = S2.solve(bd2, tol, restart=20)
     r1 = S2.solve(bd2, tol, restart=20, krylov_in_prec=2, z_prec=2)
     assert torch.equal(r0.x, r1.x)
+
+
+def test_solve_memory_of_many_columns():
+    """A small grid with many columns: the partial sums of the basis' products
+    stay an eighth of the basis, so that what a solve allocates is the basis."""
+    need_gpu()
+    n, s, m = 512, 256, 200
+    S = setup(wl.small_random((8, 8, 8), npml=1, q=50.0, seed=3), prec=2, parts=(1, 1, 1), overlap=0)
+    b = to_dev(rand_field((8, 8, 8), s, 4), S)
+    x = torch.empty_like(b)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    S.solve(b, 1e-6, restart=m, maxit=2, out=x)
+    used = before - torch.cuda.mem_get_info()[0]
+    column = 16 * n * s
+    basis = (2 * m + 3) * column + (m + 1) * column // 8     # V, Z, b, x; partial sums
+    hessenberg = 16 * s * (m + 1) * (m + 6)
+    say(f"solve memory: {used} of {basis + hessenberg}")
+    # eight blocks of columns for the local solves, 2 MB pages
+    assert used <= basis + hessenberg + 8 * column + (32 << 20)
